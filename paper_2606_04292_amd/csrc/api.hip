@@ -16,6 +16,7 @@
 #include "mp_internal.h"
 #include "host_common.h"
 #include "grid_device.h"
+#include "cycle_wg.h"
 
 namespace rs {
 void launch_root_beta(int nlev, const int *nvert, const double *hvert, double *const *beta,
@@ -149,7 +150,7 @@ struct Layout {
     size_t mp_off[kMaxLevels][6];    // RS_MIXED: delta, K32, rhs, r, dbar, psi_b (FP32)
     size_t beta_off[kMaxLevels];
     size_t soil_off[kMaxLevels];     // soil index per node (layered media)
-    size_t psi_n, psi_nm1, ks, scratch, tail, soil_tab;
+    size_t psi_n, psi_nm1, ks, scratch, soil_tab;
     size_t total;
 };
 
@@ -184,7 +185,6 @@ void plan(const rs_grid_desc *d, int precision, Layout *L)
     L->psi_nm1 = place(sizeof(double) * N0);
     L->ks = place(sizeof(double) * N0);
     L->scratch = place(sizeof(unsigned long long) * kScratchWords);
-    L->tail = place(sizeof(TailArgs));
     L->soil_tab = place(sizeof(Law) * kMaxSoils);
     L->total = off;
 }
@@ -256,9 +256,7 @@ struct rs_grid {
     unsigned long long *scratch;
     unsigned long long *host_bits;   // pinned readback
     Law *soil_tab;                    // device table of per-soil laws (layered media)
-    TailArgs *tail_dev;               // per-level records of the one-work-group cycle
-    TailArgs *tail_host;              // pinned copy
-    int tail_top;                     // first level run by it (nlev: none)
+    int tail_top;                     // first level of the one-work-group cycle (nlev: none)
     Law law;
     Law32 law32;
     bool law_set;
@@ -320,6 +318,23 @@ Law make_law(const rs_constitutive *c)
     L.newton_tol = c->newton_tol;
     L.gd_alpha = c->gd_alpha;
     L.soils = nullptr;
+    switch (c->model) {
+    case RS_HAVERKAMP:
+        L.c_th = L.hk_alpha * L.dT;
+        L.c_dth = L.unit * L.hk_beta * L.c_th;
+        break;
+    case RS_VGM:
+        L.c_th = L.dT;
+        L.c_dth = L.dT * L.vg_m * L.vg_n;
+        break;
+    case RS_GARDNER:
+        L.c_th = L.dT;
+        L.c_dth = L.gd_alpha * L.unit * L.dT;
+        break;
+    default:
+        L.c_th = L.lin_c;
+        L.c_dth = L.lin_c;
+    }
     // binom(e, k) = binom(e, k - 1) (e - k + 1) / k
     auto binom = [](double e, double *b) {
         double v = 1.0;
@@ -688,10 +703,14 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
 {
     LevelData &f = G->lev[l];
     const float a = (float)G->step.a;
-    if (l >= 1 && l >= G->tail_top && l < G->nlev - 1) {
+    if (l >= G->tail_top && l < G->nlev - 1) {
         // the rest of the correction cycle on small levels: one work-group
-        launch_vcycle_tail32(G->tail_dev, l, G->nlev - 1, G->law32, a, nu1, nu2, G->nu_coarse,
-                             G->desc.dim, G->stream);
+        WgCycle<float> A{wg_geo(f.geo), G->nlev - l, nu1, nu2, G->nu_coarse, f.dl, f.rhs32};
+        WgMems<float> M;
+        for (int q = l; q < G->nlev; ++q)
+            M.lv[q - l] = WgMem<float>{G->lev[q].K32, G->lev[q].pb32, G->lev[q].beta, nullptr,
+                                       G->lev[q].lambdaU};
+        launch_cycle_wg32(A, M, G->law32, a, G->desc.dim, G->stream);
         for (int q = l; q < G->nlev - 1; ++q)
             G->updates += (double)(nu1 + nu2) * (double)G->lev[q].unknowns;
         // the coarsest level's loop may stop after its first sweep (4-ulp exit):
@@ -742,10 +761,12 @@ int vcycle_level(rs_grid *G, int l, int nu1, int nu2)
     LevelData &f = G->lev[l];
     if (l >= G->tail_top && l < G->nlev - 1) {
         // the rest of the cycle on small levels: one work-group, one launch
-        long long nodes[kMaxLevels];
-        for (int q = 0; q < G->nlev; ++q) nodes[q] = G->lev[q].geo.N;
-        launch_vcycle_tail(G->tail_dev, l, G->nlev - 1, G->law, G->step, nu1, nu2, G->nu_coarse,
-                           G->desc.dim, nodes, G->stream);
+        WgCycle<double> A{wg_geo(f.geo), G->nlev - l, nu1, nu2, G->nu_coarse, f.psi, f.g};
+        WgMems<double> M;
+        for (int q = l; q < G->nlev; ++q)
+            M.lv[q - l] = WgMem<double>{G->lev[q].K, nullptr, G->lev[q].beta,
+                                        G->lev[q].geo.soil, G->lev[q].lambdaU};
+        launch_cycle_wg(A, M, G->law, G->step.a, G->desc.dim, G->stream);
         for (int q = l; q < G->nlev - 1; ++q)
             G->updates += (double)(nu1 + nu2) * (double)G->lev[q].unknowns;
         // the coarsest level's loop may stop after its first sweep (4-ulp exit):
@@ -809,12 +830,10 @@ double *field_ptr(const rs_grid *G, int level, int field)
 }
 
 // Fill G (a value-initialised rs_grid) as a view of a planned workspace at
-// base: level arrays, history, scratch words, the one-work-group cycle's
-// records; host_bits (kScratchWords words) and tail_host are the host-side
-// read-back and staging buffers.  Allocates nothing; queues the copy of the
-// cycle records on the stream.
-int grid_view(rs_grid *G, const rs_grid_desc *d, int precision, const Layout &L, char *base,
-              hipStream_t stream, unsigned long long *host_bits, TailArgs *tail_host)
+// base: level arrays, history, scratch words; host_bits (kScratchWords words)
+// is the host-side read-back buffer.  Allocates nothing.
+void grid_view(rs_grid *G, const rs_grid_desc *d, int precision, const Layout &L, char *base,
+               hipStream_t stream, unsigned long long *host_bits)
 {
     G->desc = *d;
     G->precision = precision;
@@ -861,53 +880,14 @@ int grid_view(rs_grid *G, const rs_grid_desc *d, int precision, const Layout &L,
     G->prof_launches = 0;
     G->prof_cells = 0.0;
     G->host_bits = host_bits;
-    G->tail_dev = (TailArgs *)(base + L.tail);
-    G->tail_host = tail_host;
-    memset(G->tail_host, 0, sizeof(TailArgs));
     G->tail_top = G->nlev;
-    for (int l = G->nlev - 1; l >= 0 && G->lev[l].geo.N <= kTailNodes && !G->lev[l].psi_alt; --l)
+    for (int l = G->nlev - 1; l >= 0 && wg_level_fits(G->lev[l].geo) && !G->lev[l].psi_alt;
+         --l)
         G->tail_top = l;
-    for (int l = 0; l < G->nlev; ++l) {
-        const LevelData &v = G->lev[l];
-        TailLevel &T = G->tail_host->lv[l];
-        const ColourMap cm = colour_map(v.geo);
-        const NodeMap nm = node_map(v.geo);
-        T.g = v.geo;
-        T.cm_total = (long long)cm.total;
-        T.H = cm.H;
-        T.n1 = cm.n1;
-        T.dH_m = cm.dH.m;
-        T.dH_s = cm.dH.s;
-        T.dN1_m = cm.dN1.m;
-        T.dN1_s = cm.dN1.s;
-        T.n0 = nm.n0;
-        T.nn1 = nm.n1;
-        T.d0_m = nm.d0.m;
-        T.d0_s = nm.d0.s;
-        T.d1_m = nm.d1.m;
-        T.d1_s = nm.d1.s;
-        T.psi = v.psi;
-        T.K = v.K;
-        T.gv = v.g;
-        T.d = v.d;
-        T.psibar = v.psibar;
-        T.beta = v.beta;
-        T.lambdaU = 0.0;
-        T.dl = v.dl;
-        T.K32 = v.K32;
-        T.rhs32 = v.rhs32;
-        T.pb32 = v.pb32;
-        T.r32 = v.r32;
-        T.dbar32 = v.dbar32;
-        T.lambdaU32 = 0.0f;
-    }
-    HIPCALL(hipMemcpyAsync(G->tail_dev, G->tail_host, sizeof(TailArgs), hipMemcpyHostToDevice,
-                           G->stream));
-    return RS_OK;
 }
 
 // Device memory of rs_bdf_step_static: the whole FP64 workspace of one grid
-// (level arrays, history, norm words, cycle records), so that the call needs
+// (level arrays, history, norm words), so that the call needs
 // no allocation.  Each device holds its own copy for the life of the process.
 static __device__ __align__(256) unsigned char scratch[RS_STATIC_WORKSPACE_BYTES];
 
@@ -918,7 +898,6 @@ constexpr int kMaxDevices = 64;
 std::mutex g_static_mu;
 void *g_static_ptr[kMaxDevices];
 unsigned long long g_static_bits[kMaxDevices][kScratchWords];
-TailArgs g_static_tail[kMaxDevices];
 
 }  // namespace
 
@@ -956,30 +935,17 @@ int rs_create_grid(const rs_grid_desc *d, int precision, void *ws_dev, size_t ws
     rs_grid *G = new (std::nothrow) rs_grid();
     if (!G) return fail(RS_ENOMEM, "host allocation failed");
     unsigned long long *bits = nullptr;
-    TailArgs *tail = nullptr;
     if (hipHostMalloc((void **)&bits, kScratchWords * sizeof(unsigned long long),
                       hipHostMallocDefault) != hipSuccess) {
         delete G;
         return fail(RS_EHIP, "hipHostMalloc failed");
     }
-    if (hipHostMalloc((void **)&tail, sizeof(TailArgs), hipHostMallocDefault) != hipSuccess) {
-        (void)hipHostFree(bits);
-        delete G;
-        return fail(RS_EHIP, "hipHostMalloc failed");
-    }
-    e = grid_view(G, d, precision, L, (char *)ws_dev, (hipStream_t)stream, bits, tail);
+    grid_view(G, d, precision, L, (char *)ws_dev, (hipStream_t)stream, bits);
     const char *gv = getenv("RS_GRAPH");
     const bool fused = G->nlev > 0 && G->lev[0].psi_alt;
-    if (!e && !(gv && gv[0] == '0') && !fused && hipStreamCreate(&G->cap) != hipSuccess) {
+    if (!(gv && gv[0] == '0') && !fused && hipStreamCreate(&G->cap) != hipSuccess) {
         (void)hipGetLastError();
         G->cap = nullptr;
-    }
-    if (e) {
-        (void)hipStreamSynchronize((hipStream_t)stream);
-        (void)hipHostFree(tail);
-        (void)hipHostFree(bits);
-        delete G;
-        return e;
     }
     *out = G;
     return RS_OK;
@@ -994,7 +960,6 @@ void rs_destroy_grid(rs_grid *G)
     if (G->cap) (void)hipStreamDestroy(G->cap);
     for (hipEvent_t ev : G->prof_ev) (void)hipEventDestroy(ev);
     if (G->host_bits) (void)hipHostFree(G->host_bits);
-    if (G->tail_host) (void)hipHostFree(G->tail_host);
     delete G;
 }
 
@@ -1122,12 +1087,7 @@ int rs_begin_step(rs_grid *G, double dt, int order)
             double v;
             memcpy(&v, &G->host_bits[1 + l], sizeof v);
             G->lev[l].lambdaU = v;
-            G->tail_host->lv[l].lambdaU = v;   // the stream is idle: the last copy is done
-            G->tail_host->lv[l].lambdaU32 = (float)v;
         }
-        if (G->tail_top < G->nlev)
-            HIPCALL(hipMemcpyAsync(G->tail_dev, G->tail_host, sizeof(TailArgs),
-                                   hipMemcpyHostToDevice, G->stream));
     }
     G->in_step = true;
     return RS_OK;
@@ -1421,8 +1381,8 @@ int rs_bdf_step_static(const rs_grid_desc *d, const rs_constitutive *c, const do
     launch_fill_u64((unsigned long long *)base, (int)(L.total / sizeof(unsigned long long)), 0ull, s);
     HIPCALL(hipGetLastError());
     rs_grid G{};
-    e = grid_view(&G, d, RS_FP64, L, (char *)base, s, g_static_bits[dev], &g_static_tail[dev]);
-    if (!e) e = rs_set_constitutive(&G, c);
+    grid_view(&G, d, RS_FP64, L, (char *)base, s, g_static_bits[dev]);
+    e = rs_set_constitutive(&G, c);
     if (!e) e = rs_set_state(&G, psi_n, psi_nm1, nstep, 0.0);
     if (e) {
         (void)hipStreamSynchronize(s);

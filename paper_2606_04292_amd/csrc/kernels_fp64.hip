@@ -17,6 +17,7 @@
 #include "grid_device.h"
 #include "transfer.h"
 #include "cell64.h"
+#include "cycle_wg.h"
 
 namespace rs {
 
@@ -960,124 +961,24 @@ __global__ __launch_bounds__(256) void k_sweep_small(Geo g, Law L, Step st, cons
     }
 }
 
-// ---------------------------------------------------------------------------
-// The cycle on the small levels of a grid in one work-group (levels of at most
-// kTailNodes nodes): the same per-node operations as the multi-launch cycle,
-// with work-group barriers between the steps instead of launches.
-// ---------------------------------------------------------------------------
-
-// n sweeps of a level; with exit set (the coarsest level) the loop stops after
-// a sweep that moved no value by more than 4 ulp: the coarse problem is then
-// solved to rounding, and further sweeps only move values within rounding.
+// The V-cycle from a level of at most kTailNodes nodes down and back in one
+// work-group (cycle_wg.h).
 template <int MODEL, bool SINK, int DIM>
-__device__ void tail_sweeps64(const TailLevel &T, const Law &L, double a, int n, bool exit = false)
+__global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg(WgCycle<double> A, WgMems<double> M,
+                                                            Law L, double a)
 {
-    const ColourMap cm = tail_cm(T);
-    for (int sw = 0; sw < n; ++sw) {
-        int changed = 0;
-        for (int colour = 0; colour < 2; ++colour) {
-            for (unsigned long long t = threadIdx.x; t < cm.total; t += blockDim.x) {
-                int i, j, k;
-                if (!colour_ijk(T.g, cm, t, colour, i, j, k)) continue;
-                if (dirichlet_t<DIM>(T.g, i, j, k)) continue;
-                changed |= ngs_cell<MODEL, SINK, DIM>(T.g, L, a, T.beta, T.lambdaU, T.K, T.gv,
-                                                      T.psi, i, j, k, colour);
-            }
-            if (colour == 0 || !exit) __syncthreads();
-            else if (!__syncthreads_or(changed)) return;
-        }
+    extern __shared__ double lds64[];
+    const Law *soils = nullptr;
+    if constexpr (MODEL == kMulti) {
+        __shared__ Law tab[kMaxSoils];
+        const int *src = (const int *)L.soils;
+        for (int t = threadIdx.x; t < (int)(sizeof(Law) / sizeof(int)) * kMaxSoils;
+             t += blockDim.x)
+            ((int *)tab)[t] = src[t];
+        soils = tab;
     }
-}
-
-// Levels lds_from..last live in LDS for the duration of the cycle (psi, K*, g,
-// d, psibar of each, with one zero element before and after every array for
-// the padded stencils): K* and, for the top level, psi and g are copied in;
-// the top level's psi is copied back (the only result used after the cycle;
-// the top level's psibar and beta stay in global memory).
-template <int MODEL, bool SINK, int DIM>
-__global__ __launch_bounds__(512) void k_vcycle_tail(const TailArgs *A, int top, int last, Law L,
-                                                     Step st, int nu1, int nu2, int nuc,
-                                                     int lds_from)
-{
-    extern __shared__ double lds[];
-    __shared__ TailLevel SL[kMaxLevels];
-    for (int l = top + (int)threadIdx.x; l <= last; l += (int)blockDim.x) SL[l] = A->lv[l];
-    __syncthreads();
-    if (lds_from <= last) {
-        if (threadIdx.x == 0) {
-            long long off = 0;
-            for (int l = lds_from; l <= last; ++l) {
-                const long long n = SL[l].g.N + 2;
-                double **arr[5] = {&SL[l].psi, &SL[l].K, &SL[l].gv, &SL[l].d, &SL[l].psibar};
-                for (int q = 0; q < 5; ++q) {
-                    if (l == top && q == 4) continue;   // read-only, stays global
-                    *arr[q] = lds + off + 1;
-                    off += n;
-                }
-            }
-        }
-        __syncthreads();
-        for (int l = lds_from; l <= last; ++l) {
-            const TailLevel &G = A->lv[l], &S = SL[l];
-            const long long N = S.g.N;
-            for (long long t = threadIdx.x; t < N + 2; t += blockDim.x) {
-                const long long u = t - 1;
-                const bool in = u >= 0 && u < N;
-                S.K[u] = in ? G.K[u] : 0.0;
-                S.psi[u] = (in && l == top) ? G.psi[u] : 0.0;
-                S.gv[u] = (in && l == top) ? G.gv[u] : 0.0;
-                S.d[u] = 0.0;
-                if (l != top) S.psibar[u] = 0.0;
-            }
-        }
-        __syncthreads();
-    }
-    const double a = st.a;
-    for (int l = top; l < last; ++l) {
-        const TailLevel &F = SL[l], &C = SL[l + 1];
-        tail_sweeps64<MODEL, SINK, DIM>(F, L, a, nu1);
-        const NodeMap nf = tail_nm(F), nc = tail_nm(C);
-        for (unsigned long long t = threadIdx.x; t < (unsigned long long)F.g.N; t += blockDim.x) {
-            int i, j, k;
-            node_ijk(nf, t, i, j, k);
-            double r = 0.0;
-            if (!dirichlet_t<DIM>(F.g, i, j, k))
-                r = F.gv[t] - apply_N_t<MODEL, SINK, DIM, true>(F.g, L, a, F.beta, F.K, F.psi, i, j, k,
-                                                          (long long)t);
-            F.d[t] = r;
-        }
-        __syncthreads();
-        for (unsigned long long t = threadIdx.x; t < (unsigned long long)C.g.N; t += blockDim.x) {
-            int i, j, k;
-            node_ijk(nc, t, i, j, k);
-            restrict_at<DIM, double>(C.g, F.g, F.psi, F.d, C.psibar, C.gv, i, j, k);
-        }
-        __syncthreads();
-        for (unsigned long long t = threadIdx.x; t < (unsigned long long)C.g.N; t += blockDim.x) {
-            int i, j, k;
-            node_ijk(nc, t, i, j, k);
-            if (!dirichlet_t<DIM>(C.g, i, j, k))
-                C.gv[t] = apply_N_t<MODEL, SINK, DIM, true>(C.g, L, a, C.beta, C.K, C.psibar, i, j, k,
-                                                      (long long)t) +
-                          C.gv[t];
-            C.psi[t] = C.psibar[t];
-        }
-        __syncthreads();
-    }
-    tail_sweeps64<MODEL, SINK, DIM>(SL[last], L, a, nuc, true);
-    for (int l = last - 1; l >= top; --l) {
-        const TailLevel &F = SL[l], &C = SL[l + 1];
-        const NodeMap nf = tail_nm(F);
-        for (unsigned long long t = threadIdx.x; t < (unsigned long long)F.g.N; t += blockDim.x) {
-            int i, j, k;
-            node_ijk(nf, t, i, j, k);
-            prolong_at<DIM, double>(F.g, C.g, C.psi, C.psibar, F.psi, i, j, k);
-        }
-        __syncthreads();
-        tail_sweeps64<MODEL, SINK, DIM>(F, L, a, nu2);
-    }
-    if (top >= lds_from)
-        for (long long t = threadIdx.x; t < SL[top].g.N; t += blockDim.x) A->lv[top].psi[t] = SL[top].psi[t];
+    typedef WgOp64<MODEL, SINK, DIM> Op;
+    wg_cycle<Op>(A, M, typename Op::Env{L, soils, a}, lds64);
 }
 
 // ---------------------------------------------------------------------------
@@ -1647,33 +1548,24 @@ void launch_prolong(const Geo &gf, const Geo &gc, const double *psi_c, const dou
     launch_prolong_t<double>(gf, gc, psi_c, psibar_c, psi_f, s);
 }
 
-struct TailLaunch {
-    const TailArgs *A; int top, last; const Law &law; const Step &st; int nu1, nu2, nuc;
-    int lds_from; size_t lds_bytes; hipStream_t s;
-    template <int M, bool S, int D>
+struct CycleWgLaunch {
+    const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; hipStream_t s;
+    template <int MO, bool S, int D>
     void go()
     {
-        hipLaunchKernelGGL((k_vcycle_tail<M, S, D>), dim3(1), dim3(512), lds_bytes, s, A, top, last,
-                           law, st, nu1, nu2, nuc, lds_from);
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
+        if (bytes > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
+                           law, a);
     }
 };
 
-size_t tail_lds_bytes(const long long *nodes, int top, int from, int last)
+void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                     int dim, hipStream_t s)
 {
-    size_t b = 0;
-    for (int l = from; l <= last; ++l) b += (l == top ? 4 : 5) * sizeof(double) * (size_t)(nodes[l] + 2);
-    return b;
-}
-
-void launch_vcycle_tail(const TailArgs *args_dev, int top, int last, const Law &law,
-                        const Step &st, int nu1, int nu2, int nuc, int dim, const long long *nodes,
-                        hipStream_t s)
-{
-    // the deepest levels that fit in kTailLds bytes of LDS
-    int from = last + 1;
-    while (from - 1 >= top && tail_lds_bytes(nodes, top, from - 1, last) <= kTailLds) --from;
-    const size_t bytes = from <= last ? tail_lds_bytes(nodes, top, from, last) : 0;
-    dispatch<true>(law, dim, TailLaunch{args_dev, top, last, law, st, nu1, nu2, nuc, from, bytes, s});
+    dispatch<true>(law, dim, CycleWgLaunch{A, M, law, a, s});
 }
 
 void launch_interp(const Geo &gf, const Geo &gc, const double *psi_c, double *psi_f, hipStream_t s)

@@ -64,6 +64,8 @@ struct Law {
     double newton_tol;   // a Newton step of at most newton_tol |x| ends the pointwise solve
     double gd_alpha;     // Gardner exponent (per law unit of psi)
     const Law *soils;    // kMulti: device table of per-soil laws, indexed by Geo::soil
+    // theta - theta_r = c_th s and theta' = c_dth ds of law_unsat (soil_device.h)
+    double c_th, c_dth;
     // binomial coefficients binom(e, k), k = 1..7, of (1 + u)^e - 1: e = hk_beta
     // (Haverkamp) or vg_n (vGM) in bin1, e = -vg_m (vGM) in bin2; the series is
     // used while |u| < series_u (2^-8, or 0 when an exponent lies outside
@@ -80,42 +82,13 @@ struct Step {
     int lag_extrap;  // BDF2 lag 2 psi^n - psi^{n-1}
 };
 
-// ---------------------------------------------------------------------------
-// Small levels in one work-group: per-level records of a grid, kept in its
-// workspace (written at creation, lambdaU refreshed at step set-up).
-// ---------------------------------------------------------------------------
-constexpr long long kTailNodes = 2049;   // levels of at most this many nodes
-
-struct TailLevel {
-    Geo g;
-    long long cm_total;
-    unsigned H, n1;
-    unsigned dH_m, dH_s, dN1_m, dN1_s;    // colour-slot division (FastDiv parts)
-    unsigned n0, nn1;
-    unsigned d0_m, d0_s, d1_m, d1_s;      // node division
-    double *psi, *K, *gv, *d, *psibar;
-    const double *beta;
-    double lambdaU;
-    // FP32 correction cycle (mixed grids; null otherwise): delta, K*, rhs,
-    // base state, inner defect, restricted delta
-    float *dl, *K32, *rhs32, *pb32, *r32, *dbar32;
-    float lambdaU32;
-};
-
-struct TailArgs {
-    TailLevel lv[kMaxLevels];
-};
+// 1-D levels of at most this many nodes run in the one-work-group cycle
+// (cycle_wg.h; 2-D and 3-D levels: wg_level_fits).
+constexpr long long kTailNodes = 2049;
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (kernels_fp64.hip)
 // ---------------------------------------------------------------------------
-// The V-cycle from level top (all of whose levels hold at most kTailNodes
-// nodes) down to level last and back, in one work-group.
-// nodes[l]: node count of level l (sizes the LDS copy of the deepest levels).
-void launch_vcycle_tail(const TailArgs *args_dev, int top, int last, const Law &law,
-                        const Step &st, int nu1, int nu2, int nuc, int dim, const long long *nodes,
-                        hipStream_t s);
-constexpr size_t kTailLds = 56 * 1024;   // LDS for the deepest levels of that cycle
 void launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t s);
 // Lexicographic (C ABI) order <-> the level's row layout; src and dst must not overlap.
 void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s);

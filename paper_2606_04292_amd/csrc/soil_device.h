@@ -47,6 +47,19 @@ constexpr double kLn2Hi = 6.93147180369123816490e-01;
 constexpr double kLn2Lo = 1.90821492927058770002e-10;
 constexpr double kInvLn2 = 1.44269504088896338700e+00;
 
+// A value that every lane of the wave holds, in a scalar register pair (there is
+// no scalar FP64 arithmetic: a product of kernel arguments lands in vector
+// registers, two per value, for as long as it lives).
+template <bool PER_LANE>
+__device__ __forceinline__ double uniform_f64(double v)
+{
+    if (PER_LANE) return v;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // p * r + c with the coefficient c in a scalar register pair (one VOP3 FMA;
 // no vector moves to materialise the constant).
 __device__ __forceinline__ double fma_sc(double p, double r, double c)
@@ -118,52 +131,6 @@ __device__ __forceinline__ double rs_exp(double y)
     return __builtin_amdgcn_ldexp(p, (int)n);
 }
 
-struct ThetaEval {
-    double th;
-    double dth;
-};
-
-template <int MODEL>
-__device__ __forceinline__ ThetaEval theta_t(const Law &L, double x)
-{
-    ThetaEval r;
-    if (MODEL == kLinear) {
-        r.th = L.tr + L.lin_c * x;
-        r.dth = L.lin_c;
-        return r;
-    }
-    if (!(x < 0.0)) {
-        r.th = L.ts;
-        r.dth = 0.0;
-        return r;
-    }
-    if (MODEL == kGardner) {
-        const double au = L.gd_alpha * L.unit;
-        const double E = rs_exp(au * x);
-        r.th = L.tr + L.dT * E;
-        r.dth = au * L.dT * E;
-        return r;
-    }
-    if (MODEL == kHaverkamp) {
-        // one reciprocal serves 1/(alpha + Q) = hu w and 1/hu = (alpha + Q) w
-        double hu = -L.unit * x;
-        double Q = rs_exp(L.hk_beta * rs_log(hu));
-        double den = L.hk_alpha + Q;
-        double w = rcp_1nr(hu * den);
-        double tmr = L.hk_alpha * L.dT * (hu * w);      // theta - theta_r
-        r.th = L.tr + tmr;
-        r.dth = L.unit * L.hk_beta * tmr * Q * w;
-        return r;
-    }
-    // van Genuchten - Mualem
-    double ax = -L.vg_alpha * x;
-    double P = rs_exp(L.vg_n * rs_log(ax));
-    double Se = rs_exp(-L.vg_m * rs_log1p(P));
-    r.th = L.tr + L.dT * Se;
-    r.dth = L.dT * L.vg_m * L.vg_n * P * Se * rcp_1nr((1.0 + P) * (-x));
-    return r;
-}
-
 // (1 + u)^e - 1 by the binomial series to u^7 (c[k - 1] = binom(e, k)), for
 // |u| < 2^-8: for -1 <= e <= 7, |binom(e, k)| <= |e| for k >= 8, so the terms left
 // out sum to at most |e| |u|^8 / (1 - |u|) < 2^-63 |e|.
@@ -179,72 +146,84 @@ __device__ __forceinline__ double pow1p_m1_series(double u, const double *c)
     return p * u;
 }
 
-// Power terms of the last law evaluation of a pointwise Newton solve.
+// Power terms of the last law evaluation at a node.
 struct PowState {
     bool ok;       // the last iterate was unsaturated (Haverkamp, vGM)
-    double x;      // that iterate
-    double ix;     // 1 / x
+    double h;      // its magnitude: unit |x| (Haverkamp), |x| (vGM)
+    double ih;     // 1 / h
     double q;      // Haverkamp: Q = (unit |x|)^beta; vGM: P = (alpha |x|)^n
     double se;     // vGM: Se = (1 + P)^-m
     double ix1p;   // vGM: 1 / (1 + P)
 };
 
-// theta and theta' at x within a Newton solve.  The power terms of the
-// Haverkamp and vGM laws scale from the last iterate's: Q(x) = Q(x') (1 + u)^beta
-// and P(x) = P(x') (1 + u)^n with u = x / x' - 1, then Se(x) = Se(x') (1 + v)^-m
-// with v = (P(x) - P(x')) / (1 + P(x')); each factor is taken by the binomial
-// series while its u or v is below L.series_u (2^-8; 0 for exponents outside
-// [-1, 7]) in magnitude, else the powers are evaluated afresh.
-template <int MODEL>
-__device__ __forceinline__ ThetaEval theta_next(const Law &L, double x, PowState &s)
+__device__ __forceinline__ PowState pow_none()
 {
-    if (MODEL != kHaverkamp && MODEL != kVgm) return theta_t<MODEL>(L, x);
-    ThetaEval r;
-    if (!(x < 0.0)) {
-        r.th = L.ts;
-        r.dth = 0.0;
-        s.ok = false;
-        return r;
-    }
-    const double u = (x - s.x) * s.ix;
-    const bool ser = s.ok && fabs(u) < L.series_u;
-    if (MODEL == kHaverkamp) {
+    return PowState{false, 0.0, 0.0, 0.0, 1.0, 0.0};
+}
+
+// The law at x < 0 within the visits of one node: theta - theta_r = L.c_th s and
+// theta' = L.c_dth ds.  The power terms of the Haverkamp and vGM laws scale from
+// the last iterate's: Q(x) = Q(x') (1 + u)^beta and P(x) = P(x') (1 + u)^n with
+// u = x / x' - 1, then Se(x) = Se(x') (1 + v)^-m with v = (P(x) - P(x')) / (1 + P(x'));
+// each factor is taken by the binomial series while its u or v is below
+// L.series_u (2^-8; 0 for exponents outside [-1, 7]) in magnitude, else the
+// powers are evaluated afresh.  A scaled power adds one rounding to the last
+// one's error (the argument u carries |u| times its own), far below the few ulp
+// times the exponent of a fresh evaluation.  NR2: two Newton-Raphson steps in
+// the reciprocal that enters theta, for values that enter a defect.
+template <int MODEL, bool NR2 = false>
+__device__ __forceinline__ void law_unsat(const Law &L, double x, PowState &p, double &s,
+                                          double &ds)
+{
+    if (MODEL == kLinear) {
+        s = x;
+        ds = 1.0;
+    } else if (MODEL == kGardner) {
+        s = rs_exp(L.gd_alpha * L.unit * x);
+        ds = s;
+    } else if (MODEL == kHaverkamp) {
         const double hu = -L.unit * x;
+        const double u = (hu - p.h) * p.ih;
         double Q;
-        if (ser) Q = fma(s.q, pow1p_m1_series(u, L.bin1), s.q);
+        if (p.ok && fabs(u) < L.series_u) Q = fma(p.q, pow1p_m1_series(u, L.bin1), p.q);
         else Q = rs_exp(L.hk_beta * rs_log(hu));
+        // one reciprocal serves 1/(alpha + Q) = hu w and 1/hu = (alpha + Q) w
         const double den = L.hk_alpha + Q;
-        const double w = rcp_1nr(hu * den);
-        const double tmr = L.hk_alpha * L.dT * (hu * w);
-        r.th = L.tr + tmr;
-        r.dth = L.unit * L.hk_beta * tmr * Q * w;
-        s.q = Q;
-        s.ix = -L.unit * (den * w);   // 1/x = -unit / hu
+        const double w = NR2 ? rcp_nr(hu * den) : rcp_1nr(hu * den);
+        s = hu * w;
+        ds = Q * (s * w);
+        p.q = Q;
+        p.h = hu;
+        p.ih = den * w;
+        p.ok = true;
     } else {
-        double P, Se;
-        bool fresh = !ser;
-        if (ser) {
-            const double dP = s.q * pow1p_m1_series(u, L.bin1);
-            const double v = dP * s.ix1p;
-            P = s.q + dP;
-            if (fabs(v) < L.series_u) Se = fma(s.se, pow1p_m1_series(v, L.bin2), s.se);
-            else fresh = true;
+        const double h = -x;
+        const double u = (h - p.h) * p.ih;
+        double P = 0.0;
+        bool fresh = true;
+        if (p.ok && fabs(u) < L.series_u) {
+            const double dP = p.q * pow1p_m1_series(u, L.bin1);
+            const double v = dP * p.ix1p;
+            P = p.q + dP;
+            if (fabs(v) < L.series_u) {
+                s = fma(p.se, pow1p_m1_series(v, L.bin2), p.se);
+                fresh = false;
+            }
         }
         if (fresh) {
-            P = rs_exp(L.vg_n * rs_log(-L.vg_alpha * x));
-            Se = rs_exp(-L.vg_m * rs_log1p(P));
+            P = rs_exp(L.vg_n * rs_log(L.vg_alpha * h));
+            s = rs_exp(-L.vg_m * rs_log1p(P));
         }
-        const double w = rcp_1nr((1.0 + P) * (-x));
-        r.th = L.tr + L.dT * Se;
-        r.dth = L.dT * L.vg_m * L.vg_n * P * Se * w;
-        s.q = P;
-        s.se = Se;
-        s.ix = -(1.0 + P) * w;
-        s.ix1p = -x * w;
+        const double X = 1.0 + P;
+        const double w = rcp_1nr(X * h);
+        ds = P * (s * w);
+        p.q = P;
+        p.se = s;
+        p.h = h;
+        p.ih = X * w;
+        p.ix1p = h * w;
+        p.ok = true;
     }
-    s.x = x;
-    s.ok = true;
-    return r;
 }
 
 template <int MODEL>
@@ -312,94 +291,122 @@ __device__ __forceinline__ void feddes(const Law &L, double x, double &a, double
 // the step leaves the iterate unchanged.  A Newton step (not a bisection) that
 // moves x by at most L.newton_tol |x_new| ends the solve for that cell: the
 // steps left out would move it by about that step squared times F''/2F'.
-template <int MODEL, bool SINK, int NEWTON>
-__device__ __forceinline__ double local_solve_t(const Law &L, double a, double beta, double c,
-                                                double f, double x0)
+// ic = rcp_nr(c) (unused by the linear law); ps: the power terms of the node's
+// last evaluation (pow_none() if there is none), left at those of the solve's
+// last one.  A wave issues one instruction every 6 to 7 cycles whatever its
+// kind, so the loop is written for few of them: F as v + (c x - (f - a theta_r))
+// with v = a (theta - theta_r), uniform factors of the law formed once, selects
+// instead of branches, the bisection only where some lane needs it.
+// PER_LANE: the law differs between lanes (layered media).
+template <int MODEL, bool SINK, int NEWTON, bool PER_LANE = false>
+__device__ __forceinline__ double local_solve_ic(const Law &L, double a, double beta, double c,
+                                                 double ic, double f, double x0, PowState &ps)
 {
+    const double ath = uniform_f64<PER_LANE>(a * L.c_th), adth = uniform_f64<PER_LANE>(a * L.c_dth);
+    const double as = uniform_f64<PER_LANE>(a * L.dT);
+    const double fr = f - a * L.tr;
     double lo, hi;
     if (MODEL == kLinear) {
         lo = -INFINITY;
         hi = INFINITY;
     } else {
-        double ic = rcp_nr(c);
         lo = (f - a * L.ts - beta) * ic;
-        hi = (f - a * L.tr) * ic;
-        double pad = 1e-12 * (fabs(lo) + fabs(hi));
+        hi = fr * ic;
+        const double pad = 1e-12 * (fabs(lo) + fabs(hi));
         lo -= pad;
         hi += pad;
     }
     double x = x0;
     bool done = false;
-    PowState ps;
-    ps.ok = false;
-    ps.x = 0.0;
-    ps.ix = 0.0;
-    ps.q = 0.0;
-    ps.se = 1.0;
-    ps.ix1p = 0.0;
     const int iters = NEWTON > 0 ? NEWTON : L.newton;
     for (int k = 0; k < iters; ++k) {
-        ThetaEval t = theta_next<MODEL>(L, x, ps);
-        double F = a * t.th + c * x - f;
-        double dF = a * t.dth + c;
+        double v = as, dF = c;   // saturated: theta_s, theta' = 0
+        if (MODEL == kLinear || x < 0.0) {
+            double s, ds;
+            law_unsat<MODEL>(L, x, ps, s, ds);
+            v = ath * s;
+            dF = fma(adth, ds, c);
+        } else {
+            ps.ok = false;
+        }
+        double F = v + fma(c, x, -fr);
         if (SINK) {
             double fa, dfa;
             feddes(L, x, fa, dfa);
             F += beta * fa;
             dF += beta * dfa;
         }
-        if (F > 0.0) {
-            hi = fmin(hi, x);
-        } else if (F < 0.0) {
-            lo = fmax(lo, x);
-        } else {
-            lo = x;
-            hi = x;
-        }
-        double xn = x - F * rcp_1nr(dF);
-        const bool bisect = !(dF > 0.0) || (xn != x && !(xn > lo && xn < hi));
+        // x becomes an end of the bracket by the sign of F (both at a root, or
+        // where F is not a number: the value then stays)
+        const bool pos = F > 0.0, neg = F < 0.0;
+        const bool end = !pos & !neg;
+        hi = ((pos & !(hi <= x)) | end) ? x : hi;
+        lo = ((neg & !(lo >= x)) | end) ? x : lo;
+        double xn = fma(-F, rcp_1nr(dF), x);
+        const bool bisect = !(dF > 0.0) | ((xn != x) & !((xn > lo) & (xn < hi)));
         if (bisect) xn = 0.5 * (lo + hi);
-        const bool small = !bisect && fabs(xn - x) <= L.newton_tol * fabs(xn);
+        const bool small = !bisect & (fabs(xn - x) <= L.newton_tol * fabs(xn));
         // lanes whose solve has ended keep their value while the rest of the
         // wave iterates; the wave leaves once every lane has ended
-        if (!done) x = xn;
-        done = done || small;
-        if (__all(done)) break;
+        x = done ? x : xn;
+        done = done | small;
+        if (__builtin_amdgcn_ballot_w64(!done) == 0) break;
     }
     return x;
 }
 
-__device__ __forceinline__ double local_solve(const Law &L, double a, double beta, double c,
-                                              double f, double x0)
+template <int MODEL, bool SINK, int NEWTON>
+__device__ __forceinline__ double local_solve_t(const Law &L, double a, double beta, double c,
+                                                double f, double x0)
 {
-    const bool s = L.sink == kSinkFeddes;
-    switch (L.model) {
-    case kGardner:
-        return s ? local_solve_t<kGardner, true, 0>(L, a, beta, c, f, x0)
-                 : local_solve_t<kGardner, false, 0>(L, a, beta, c, f, x0);
-    case kHaverkamp:
-        return s ? local_solve_t<kHaverkamp, true, 0>(L, a, beta, c, f, x0)
-                 : local_solve_t<kHaverkamp, false, 0>(L, a, beta, c, f, x0);
-    case kVgm:
-        return s ? local_solve_t<kVgm, true, 0>(L, a, beta, c, f, x0)
-                 : local_solve_t<kVgm, false, 0>(L, a, beta, c, f, x0);
-    default:
-        return s ? local_solve_t<kLinear, true, 0>(L, a, beta, c, f, x0)
-                 : local_solve_t<kLinear, false, 0>(L, a, beta, c, f, x0);
-    }
+    PowState ps = pow_none();
+    return local_solve_ic<MODEL, SINK, NEWTON>(L, a, beta, c,
+                                               MODEL == kLinear ? 0.0 : rcp_nr(c), f, x0, ps);
 }
 
 // The pointwise solve with the law of one soil picked at run time (layered
 // media): the same iteration as local_solve_t for that soil's model.
 template <bool SINK, int NEWTON>
+__device__ __forceinline__ double local_solve_soil_ic(const Law &Ls, double a, double beta,
+                                                      double c, double ic, double f, double x0,
+                                                      PowState &ps)
+{
+    switch (Ls.model) {
+    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
+    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
+    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
+    default: return local_solve_ic<kLinear, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
+    }
+}
+
+template <bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_soil(const Law &Ls, double a, double beta, double c,
                                                    double f, double x0)
 {
-    switch (Ls.model) {
-    case kGardner: return local_solve_t<kGardner, SINK, NEWTON>(Ls, a, beta, c, f, x0);
-    case kHaverkamp: return local_solve_t<kHaverkamp, SINK, NEWTON>(Ls, a, beta, c, f, x0);
-    case kVgm: return local_solve_t<kVgm, SINK, NEWTON>(Ls, a, beta, c, f, x0);
-    default: return local_solve_t<kLinear, SINK, NEWTON>(Ls, a, beta, c, f, x0);
+    PowState ps = pow_none();
+    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0, ps);
+}
+
+// theta at x for a defect, from the power terms of the node's last evaluation.
+template <int MODEL>
+__device__ __forceinline__ double theta_defect(const Law &L, double x, PowState &ps)
+{
+    if constexpr (MODEL == kMulti) {
+        switch (L.model) {
+        case kHaverkamp: return theta_defect<kHaverkamp>(L, x, ps);
+        case kVgm: return theta_defect<kVgm>(L, x, ps);
+        default: return theta_only(L, x);
+        }
+    } else if constexpr (MODEL == kHaverkamp || MODEL == kVgm) {
+        if (!(x < 0.0)) {
+            ps.ok = false;
+            return L.ts;
+        }
+        double s, ds;
+        law_unsat<MODEL, true>(L, x, ps, s, ds);
+        return L.tr + L.c_th * s;
+    } else {
+        return theta_only_t<MODEL>(L, x);
     }
 }
 

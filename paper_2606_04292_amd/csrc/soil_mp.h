@@ -248,21 +248,18 @@ __device__ __forceinline__ float feddes_value32(const Law32 &L, float x)
 // Scalar correction update: a dtheta(d) + beta da(d) + c d = f by the same
 // safeguarded Newton iteration as the FP64 smoother (bracket from the room
 // theta has to move and the sink range, widened by 1e-6 of its ends), ending
-// after a Newton step of at most newton_tol |d|.
+// after a Newton step of at most newton_tol |d|.  Of the base state: up and
+// down (base_room) and the stress factor ab; ic = 1 / c.
 template <int MODEL, bool SINK>
-__device__ __forceinline__ float local_solve32(const Law32 &L, float a, float beta, float c,
-                                               float f, const Base &b, float d0)
+__device__ __forceinline__ float local_solve32_ic(const Law32 &L, float a, float beta, float c,
+                                                  float ic, float f, const Base &b, float up,
+                                                  float down, float ab, float d0)
 {
     float lo, hi;
     if (MODEL == kLinear) {
         lo = -INFINITY;
         hi = INFINITY;
     } else {
-        float up, down;
-        base_room<MODEL>(L, b, up, down);
-        float ab = 0.0f;
-        if (SINK) ab = feddes_value32(L, b.psi);
-        const float ic = f_rcp(c);
         lo = (f - a * up - (SINK ? beta * (1.0f - ab) : 0.0f)) * ic;
         hi = (f + a * down + (SINK ? beta * ab : 0.0f)) * ic;
         const float pad = 1e-6f * (fabsf(lo) + fabsf(hi));
@@ -282,18 +279,30 @@ __device__ __forceinline__ float local_solve32(const Law32 &L, float a, float be
             F += beta * da;
             dF += beta * ds;
         }
-        if (F > 0.0f) hi = fminf(hi, d);
-        else if (F < 0.0f) lo = fmaxf(lo, d);
-        else { lo = d; hi = d; }
+        // selects instead of branches (see local_solve_ic)
+        const bool pos = F > 0.0f, neg = F < 0.0f;
+        const bool end = !pos & !neg;
+        hi = ((pos & !(hi <= d)) | end) ? d : hi;
+        lo = ((neg & !(lo >= d)) | end) ? d : lo;
         float dn = d - F * f_rcp(dF);
-        const bool bisect = !(dF > 0.0f) || (dn != d && !(dn > lo && dn < hi));
+        const bool bisect = !(dF > 0.0f) | ((dn != d) & !((dn > lo) & (dn < hi)));
         if (bisect) dn = 0.5f * (lo + hi);
-        const bool small = !bisect && fabsf(dn - d) <= L.newton_tol * fabsf(dn);
-        if (!done) d = dn;
-        done = done || small;
-        if (__all(done)) break;
+        const bool small = !bisect & (fabsf(dn - d) <= L.newton_tol * fabsf(dn));
+        d = done ? d : dn;
+        done = done | small;
+        if (__builtin_amdgcn_ballot_w64(!done) == 0) break;
     }
     return d;
+}
+
+template <int MODEL, bool SINK>
+__device__ __forceinline__ float local_solve32(const Law32 &L, float a, float beta, float c,
+                                               float f, const Base &b, float d0)
+{
+    float up, down;
+    base_room<MODEL>(L, b, up, down);
+    const float ab = SINK ? feddes_value32(L, b.psi) : 0.0f;
+    return local_solve32_ic<MODEL, SINK>(L, a, beta, c, f_rcp(c), f, b, up, down, ab, d0);
 }
 
 }  // namespace rs
