@@ -43,9 +43,9 @@ COUNTERS_PROFILE = os.path.join(ROOT, "profiles", "sweep_fp64_block3d_haverkamp_
 # The translation units of the FP64 and FP32 sweep kernels: their counters
 # stay valid while these sources are unchanged.
 SWEEP_SOURCES = ["kernels_fp64.hip", "rs_internal.h", "soil_device.h", "grid_device.h",
-                 "transfer.h", "cell64.h", "cycle_wg.h", "soil_mp.h"]
+                 "transfer.h", "cell64.h"]
 SWEEP32_SOURCES = ["kernels_mp.hip", "rs_internal.h", "soil_device.h", "grid_device.h",
-                   "transfer.h", "soil_mp.h", "cell32.h", "cycle_wg.h"]
+                   "transfer.h", "soil_mp.h", "cell32.h", "mp_internal.h"]
 
 
 def kernel_sources_sha256(sources=SWEEP_SOURCES):

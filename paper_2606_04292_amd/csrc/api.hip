@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <vector>
@@ -16,7 +17,7 @@
 #include "mp_internal.h"
 #include "host_common.h"
 #include "grid_device.h"
-#include "cycle_wg.h"
+#include "cycle_tile.h"
 
 namespace rs {
 void launch_root_beta(int nlev, const int *nvert, const double *hvert, double *const *beta,
@@ -254,7 +255,9 @@ struct rs_grid {
     bool has_ks;
     int coarse_k;                     // RS_COARSE_INJECT or RS_COARSE_FW
     unsigned long long *scratch;
-    unsigned long long *host_bits;   // pinned readback
+    unsigned long long *host_bits;   // readback words
+    unsigned long long *host_dev;    // their device address (pinned; null on static grids)
+    hipEvent_t norm_ev;               // a norm has reached host_bits (with host_dev)
     Law *soil_tab;                    // device table of per-soil laws (layered media)
     int tail_top;                     // first level of the one-work-group cycle (nlev: none)
     Law law;
@@ -491,50 +494,76 @@ int sweep_level(rs_grid *G, int l, int nsweeps)
     return RS_OK;
 }
 
-int read_norm(rs_grid *G, double *out)
+// The norm word's way to the host: queued behind the kernel that formed it
+// (norm_send), read once it has arrived (norm_wait; what was queued in between
+// keeps running).  The word is zero again for the next norm.
+int norm_send(rs_grid *G)
 {
+    if (G->host_dev) {
+        launch_norm_out(G->scratch, G->host_dev, G->stream);
+        HIPCALL(hipGetLastError());
+        HIPCALL(hipEventRecord(G->norm_ev, G->stream));
+        return RS_OK;
+    }
     HIPCALL(hipMemcpyAsync(G->host_bits, G->scratch, sizeof(unsigned long long),
                            hipMemcpyDeviceToHost, G->stream));
-    HIPCALL(hipStreamSynchronize(G->stream));
+    launch_fill_u64(G->scratch, 1, 0ull, G->stream);
+    HIPCALL(hipGetLastError());
+    return RS_OK;
+}
+
+int norm_wait(rs_grid *G, double *out)
+{
+    if (G->host_dev) HIPCALL(hipEventSynchronize(G->norm_ev));
+    else HIPCALL(hipStreamSynchronize(G->stream));
     if (G->prof_used) {
         int e = harvest_profile(G);
         if (e) return e;
     }
-    unsigned long long b = G->host_bits[0];
-    double v;
-    memcpy(&v, &b, sizeof v);
-    *out = v;
+    const unsigned long long b = __atomic_load_n(G->host_bits, __ATOMIC_RELAXED);
+    memcpy(out, &b, sizeof b);
     return RS_OK;
 }
 
-// FP64 defect max-norm of the finest level (and the defect vector into d; or,
-// with mp_start, the start of an FP32 correction: rhs = fl32(defect),
-// psi_b = fl32(psi), delta = 0).
-int fine_norm(rs_grid *G, double *out, double *d = nullptr, bool mp_start = false)
+// FP64 defect max-norm of the finest level, on its way to the host (and the
+// defect vector into d; or, with mp_start, the start of an FP32 correction:
+// rhs = fl32(defect), psi_b = fl32(psi), delta = 0).
+int fine_norm_send(rs_grid *G, double *d = nullptr, bool mp_start = false)
 {
     LevelData &f = G->lev[0];
-    launch_fill_u64(G->scratch, 1, 0ull, G->stream);
     MpStart mp{};
     if (mp_start) mp = MpStart{f.rhs32, f.pb32, f.dl};
     launch_residual(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, d, G->scratch, G->stream, mp);
-    HIPCALL(hipGetLastError());
-    return read_norm(G, out);
+    return norm_send(G);
 }
 
+int fine_norm(rs_grid *G, double *out, double *d = nullptr, bool mp_start = false)
+{
+    int e = fine_norm_send(G, d, mp_start);
+    return e ? e : norm_wait(G, out);
+}
+
+bool tile_level(const rs_grid *G, int l);
+template <typename T>
+void tile_phase(rs_grid *G, int l, int phase, int nu, unsigned long long *norm);
+
 // The pre-smoothing of an FP64 cycle on the finest level and the max-norm of
-// the defect it leaves (the defect vector into d): where the level runs the
+// the defect it leaves, on its way to the host (the defect vector into d): where the level runs the
 // pair sweep, the last colour pass forms the defect of its nodes on the way
 // and one more pass that of the others; otherwise the sweeps, then the defect
-// kernel.  The same d and norm either way.
-int presmooth_norm(rs_grid *G, int nu1, double *out)
+// kernel.  The same d and norm either way.  A tiled level leaves the smoothed
+// iterate in d instead, and its coarse level ready.
+int presmooth_send(rs_grid *G, int nu1)
 {
     LevelData &f = G->lev[0];
+    if (tile_level(G, 0)) {
+        tile_phase<double>(G, 0, kTileDown, nu1, G->scratch);
+        return norm_send(G);
+    }
     if (f.psi_alt || !sweep_defect_level(f.geo, G->law, nu1)) {
         int e = sweep_level(G, 0, nu1);
-        if (e) return e;
-        return fine_norm(G, out, f.d);
+        return e ? e : fine_norm_send(G, f.d);
     }
-    launch_fill_u64(G->scratch, 1, 0ull, G->stream);
     // the plain colour passes are timed like any sweep batch of the level
     const bool timed = G->prof_on;
     if (timed) {
@@ -551,9 +580,8 @@ int presmooth_norm(rs_grid *G, int nu1, double *out)
     }
     launch_sweep_defect(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, nu1, f.d, G->scratch, 1,
                         G->stream);
-    HIPCALL(hipGetLastError());
     G->updates += (double)nu1 * (double)f.unknowns;
-    return read_norm(G, out);
+    return norm_send(G);
 }
 
 // Scale of the defect's rounding floor on the finest level: the largest sum
@@ -605,20 +633,186 @@ void sweep32_level(rs_grid *G, int l, int nsweeps)
 
 int vcycle_level(rs_grid *G, int l, int nu1, int nu2);
 void vcycle32_level(rs_grid *G, int l, int nu1, int nu2);
+int coarse_cycle(rs_grid *G, int which, int nu1, int nu2);
+
+// ---------------------------------------------------------------------------
+// Tiled levels (cycle_tile.h)
+// ---------------------------------------------------------------------------
+
+// Levels that run in tiles: 1-D and 2-D levels above the one-work-group cycle
+// of at most kTileMaxNodes nodes.  A V(2,2) visit of a vGM level, plain
+// launches against tiles (us of kernel time): 129^2 53 against 29, 257^2 55
+// against 30, but 513^2 66 against 91, where the 4.3 loads of the halo make
+// the tiles' arithmetic the longer way.  RS_SWEEP (any sweep kernel picked by
+// hand) and profiling of the finest level's colour passes keep the plain
+// launches.
+constexpr long long kTileMaxNodes = 1ll << 17;
+
+bool tile_level(const rs_grid *G, int l)
+{
+    const Geo &g = G->lev[l].geo;
+    if (g.dim > 2 || l >= G->tail_top || l >= G->nlev - 1 || G->lev[l].psi_alt ||
+        g.N > kTileMaxNodes || (l == 0 && G->prof_on) || getenv("RS_SWEEP"))
+        return false;
+    // the smallest halo of a sweep and of a transfer with one sweep fit
+    int own[2], tiles[2];
+    return tile_shape(g, 6, own, tiles);
+}
+
+// One launch of a tiled phase with ns sweeps: its halo, tiles, and an estimate
+// of its time in us (12 to 15 measured for a launch with four colour passes on
+// up to 512 tiles, the two work-groups per CU that are resident; a launch of
+// which 3 are dispatch, arguments and the loads, a pass and the transfer about
+// 1.5 each for the vGM law).
+struct TilePlan {
+    int ns, halo, own[2], tiles[2];
+    double cost;
+};
+
+bool tile_plan(const Geo &g, int phase, int ns, TilePlan *p)
+{
+    p->ns = ns;
+    p->halo = 2 * ns + (phase == kTileDown ? 4 : 0);
+    if (p->halo == 0) p->halo = 2;
+    if (!tile_shape(g, p->halo, p->own, p->tiles)) return false;
+    const double rounds = p->tiles[0] * p->tiles[1] / 512.0;
+    const double work = 3.0 + 1.5 * (2 * ns + (phase == kTileDown ? 3 : 1));
+    p->cost = 3.0 + work * (rounds > 1.0 ? rounds : 1.0);
+    return true;
+}
+
+// nu sweeps of a phase as an odd number of launches (the iterate alternates
+// between two arrays and ends in the other one): one with the transfer (the
+// last going down, the first going up) and `more` of sweeps only, the first
+// `longer` of which take one sweep more than the rest; the cheapest split by
+// tile_plan's estimate.
+struct TileSplit {
+    TilePlan transfer, sweep, sweep1;   // sweep1: one sweep more
+    int more, longer;
+};
+
+bool tile_split(const Geo &g, int phase, int nu, TileSplit *out)
+{
+    bool found = false;
+    double cost = 0.0;
+    int best = 0;
+    for (int k = 1; k == 1 || k <= nu; k += 2) {
+        if (found && k > best + 8) break;
+        TileSplit t;
+        const int ns = nu / k;
+        t.more = k - 1;
+        t.longer = nu % k;
+        if (!tile_plan(g, phase, ns, &t.transfer)) continue;
+        if (t.more > t.longer && !tile_plan(g, kTileSweep, ns, &t.sweep)) continue;
+        if (t.longer > 0 && !tile_plan(g, kTileSweep, ns + 1, &t.sweep1)) continue;
+        double c = t.transfer.cost;
+        if (t.more > t.longer) c += (t.more - t.longer) * t.sweep.cost;
+        if (t.longer > 0) c += t.longer * t.sweep1.cost;
+        if (found && c >= cost) continue;
+        *out = t;
+        cost = c;
+        best = k;
+        found = true;
+    }
+    return found;
+}
+
+template <typename T> struct TileLevelData;   // the arrays of a level a tiled phase works on
+template <> struct TileLevelData<double> {
+    static double *x(const LevelData &v) { return v.psi; }
+    static double *y(const LevelData &v) { return v.d; }
+    static double *rhs(const LevelData &v) { return v.g; }
+    static const double *K(const LevelData &v) { return v.K; }
+    static const double *pb(const LevelData &) { return nullptr; }
+    static double *bar(const LevelData &v) { return v.psibar; }
+    static void launch(const rs_grid *G, const TileArgs<double> &A, int phase, const TilePlan &p,
+                       size_t words)
+    {
+        launch_tile(A, phase, p.tiles[0] * p.tiles[1], words, G->law, G->step.a, G->stream);
+    }
+};
+template <> struct TileLevelData<float> {
+    static float *x(const LevelData &v) { return v.dl; }
+    static float *y(const LevelData &v) { return v.r32; }
+    static float *rhs(const LevelData &v) { return v.rhs32; }
+    static const float *K(const LevelData &v) { return v.K32; }
+    static const float *pb(const LevelData &v) { return v.pb32; }
+    static float *bar(const LevelData &v) { return v.dbar32; }
+    static void launch(const rs_grid *G, const TileArgs<float> &A, int phase, const TilePlan &p,
+                       size_t words)
+    {
+        launch_tile32(A, phase, p.tiles[0] * p.tiles[1], words, G->law32, (float)G->step.a,
+                      G->stream);
+    }
+};
+
+// A tiled phase of level l: down reads the iterate and leaves the smoothed one
+// in the level's second array (FP64: d, FP32: r32), the coarser level ready for
+// its cycle and, with norm set, the defect's max-norm folded into it (FP64);
+// up reads the second array and leaves the iterate in place.
+template <typename T>
+void tile_phase(rs_grid *G, int l, int phase, int nu, unsigned long long *norm)
+{
+    typedef TileLevelData<T> D;
+    const LevelData &f = G->lev[l], &c = G->lev[l + 1];
+    TileSplit sp;
+    if (!tile_split(f.geo, phase, nu, &sp)) return;   // tile_level has checked the shape
+    TileArgs<T> A{};
+    A.g = wg_geo(f.geo);
+    A.dim = f.geo.dim;
+    A.rhs = D::rhs(f);
+    A.K = D::K(f);
+    A.pb = D::pb(f);
+    A.beta = f.beta;
+    A.soil = f.geo.soil;
+    A.lambdaU = f.lambdaU;
+    A.bar = D::bar(c);
+    A.rhsc = D::rhs(c);
+    A.xc = D::x(c);
+    A.Kc = D::K(c);
+    A.pbc = D::pb(c);
+    A.betac = c.beta;
+    A.soilc = c.geo.soil;
+    T *from = phase == kTileDown ? D::x(f) : D::y(f), *to = phase == kTileDown ? D::y(f) : D::x(f);
+    for (int q = 0; q <= sp.more; ++q) {
+        const bool transfer = q == (phase == kTileDown ? sp.more : 0);
+        const int m = phase == kTileDown ? q : q - 1;   // index among the sweep launches
+        const TilePlan &p = transfer ? sp.transfer : (m < sp.longer ? sp.sweep1 : sp.sweep);
+        for (int t = 0; t < 2; ++t) A.own[t] = p.own[t];
+        A.halo = p.halo;
+        A.tiles0 = p.tiles[0];
+        A.ns = p.ns;
+        A.x = from;
+        A.y = to;
+        A.norm = transfer ? norm : nullptr;
+        D::launch(G, A, transfer ? phase : kTileSweep, p,
+                  tile_lds_words(f.geo.dim, f.geo, p.halo, p.own));
+        T *t = from;
+        from = to;
+        to = t;
+    }
+    G->updates += (double)nu * (double)f.unknowns;
+}
 
 // The part of a V-cycle below the finest level, as plain launches: the
 // restriction of the fine iterate and of its defect (FP64: already in the
-// level's d), the coarse right-hand side, the cycle on level 1 and below, the
-// prolongation.  which = 1: the FP32 correction cycle, which first forms its
-// inner defect (the coarse levels hold the injected base state psi_b).
+// level's d), the coarse right-hand side, the cycle on level 1 and below.  It
+// leaves the fine iterate alone.  which = 1: the FP32 correction cycle, which
+// first forms its inner defect (the coarse levels hold the injected base
+// state psi_b).
 void coarse_cycle_plain(rs_grid *G, int which, int nu1, int nu2)
 {
     LevelData &f = G->lev[0], &c = G->lev[1];
+    if (tile_level(G, 0)) {
+        // the finest level's transfers are part of its tiled phases
+        if (which == 0) vcycle_level(G, 1, nu1, nu2);
+        else vcycle32_level(G, 1, nu1, nu2);
+        return;
+    }
     if (which == 0) {
         launch_restrict(c.geo, f.geo, f.psi, f.d, c.psibar, c.g, G->stream);
         launch_coarse_rhs(c.geo, G->law, G->step, c.beta, c.K, c.psibar, c.g, c.psi, G->stream);
         vcycle_level(G, 1, nu1, nu2);
-        launch_prolong(f.geo, c.geo, c.psi, c.psibar, f.psi, G->stream);
         return;
     }
     const float a = (float)G->step.a;
@@ -626,13 +820,32 @@ void coarse_cycle_plain(rs_grid *G, int which, int nu1, int nu2)
     launch_restrict32(c.geo, f.geo, f.dl, f.r32, c.dbar32, c.rhs32, G->stream);
     launch_coarse_rhs32(c.geo, G->law32, a, c.beta, c.K32, c.pb32, c.dbar32, c.rhs32, c.dl, G->stream);
     vcycle32_level(G, 1, nu1, nu2);
-    launch_prolong32(f.geo, c.geo, c.dl, c.dbar32, f.dl, G->stream);
+}
+
+// The way back to the finest level after coarse_cycle: prolongation and
+// post-smoothing.
+int fine_up(rs_grid *G, int which, int nu2)
+{
+    LevelData &f = G->lev[0], &c = G->lev[1];
+    if (tile_level(G, 0)) {
+        if (which == 0) tile_phase<double>(G, 0, kTileUp, nu2, nullptr);
+        else tile_phase<float>(G, 0, kTileUp, nu2, nullptr);
+        return RS_OK;
+    }
+    if (which == 1) {
+        launch_prolong32(f.geo, c.geo, c.dl, c.dbar32, f.dl, G->stream);
+        sweep32_level(G, 0, nu2);
+        return RS_OK;
+    }
+    launch_prolong(f.geo, c.geo, c.psi, c.psibar, f.psi, G->stream);
+    return sweep_level(G, 0, nu2);
 }
 
 // What the coarse-cycle graph bakes into its kernel arguments.
 struct CycleKey {
     double a, dt;
     int order, lag_extrap, nu1, nu2, nu_coarse, law_version;
+    int tiles;   // bit l: level l runs in tiles
     double lambdaU[kMaxLevels];
 };
 
@@ -657,7 +870,10 @@ int coarse_cycle(rs_grid *G, int which, int nu1, int nu2)
     k.nu2 = nu2;
     k.nu_coarse = G->nu_coarse;
     k.law_version = G->law_version;
-    for (int l = 0; l < G->nlev; ++l) k.lambdaU[l] = G->lev[l].lambdaU;
+    for (int l = 0; l < G->nlev; ++l) {
+        k.lambdaU[l] = G->lev[l].lambdaU;
+        k.tiles |= (tile_level(G, l) ? 1 : 0) << l;
+    }
     if (!G->cg[which] || memcmp(&k, G->cg_key[which], sizeof k) != 0) {
         if (G->cg[which]) {
             HIPCALL(hipStreamSynchronize(G->stream));   // a replay may still run
@@ -698,6 +914,15 @@ int coarse_cycle(rs_grid *G, int which, int nu1, int nu2)
     return RS_OK;
 }
 
+// The FP32 correction cycle from the finest level down to its coarse part's end
+// (grids above the one-work-group cycle).
+void fine_down32(rs_grid *G, int nu1, int nu2)
+{
+    if (tile_level(G, 0)) tile_phase<float>(G, 0, kTileDown, nu1, nullptr);
+    else sweep32_level(G, 0, nu1);
+    (void)coarse_cycle(G, 1, nu1, nu2);
+}
+
 // FP32 FAS V-cycle on the correction equation (same structure as the FP64 one).
 void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
 {
@@ -723,9 +948,14 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
         return;
     }
     if (l == 0) {
-        sweep32_level(G, 0, nu1);
-        (void)coarse_cycle(G, 1, nu1, nu2);
-        sweep32_level(G, 0, nu2);
+        fine_down32(G, nu1, nu2);
+        (void)fine_up(G, 1, nu2);
+        return;
+    }
+    if (tile_level(G, l)) {
+        tile_phase<float>(G, l, kTileDown, nu1, nullptr);
+        vcycle32_level(G, l + 1, nu1, nu2);
+        tile_phase<float>(G, l, kTileUp, nu2, nullptr);
         return;
     }
     LevelData &c = G->lev[l + 1];
@@ -742,9 +972,10 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
 // right-hand side fl32(r), the base state fl32(psi) and delta = 0 on the finest
 // level (fine_norm with mp_start); psi_b is injected into the coarse levels
 // once, FP32 cycles solve the correction equation and psi += delta in FP64.
-void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
+// The head (injection, the first cycle down to the end of its coarse part)
+// touches FP32 arrays only.
+void mp_head(rs_grid *G, int nu1, int nu2)
 {
-    LevelData &f = G->lev[0];
     Geo geo[kMaxLevels];
     float *pb[kMaxLevels];
     for (int l = 0; l < G->nlev; ++l) {
@@ -752,8 +983,22 @@ void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
         pb[l] = G->lev[l].pb32;
     }
     launch_inject_base32(geo, pb, G->nlev, G->stream);
-    for (int c = 0; c < inner; ++c) vcycle32_level(G, 0, nu1, nu2);
+    if (G->tail_top > 0 && G->nlev > 1) fine_down32(G, nu1, nu2);
+    else vcycle32_level(G, 0, nu1, nu2);
+}
+
+void mp_tail(rs_grid *G, int inner, int nu1, int nu2)
+{
+    LevelData &f = G->lev[0];
+    if (G->tail_top > 0 && G->nlev > 1) (void)fine_up(G, 1, nu2);
+    for (int c = 1; c < inner; ++c) vcycle32_level(G, 0, nu1, nu2);
     launch_apply_delta(f.geo.N, f.dl, f.psi, G->stream);
+}
+
+void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
+{
+    mp_head(G, nu1, nu2);
+    mp_tail(G, inner, nu1, nu2);
 }
 
 int vcycle_level(rs_grid *G, int l, int nu1, int nu2)
@@ -776,11 +1021,21 @@ int vcycle_level(rs_grid *G, int l, int nu1, int nu2)
     }
     if (l == G->nlev - 1) return sweep_level(G, l, G->nu_coarse);
     if (l == 0) {
-        int e = sweep_level(G, 0, nu1);
-        if (e) return e;
-        launch_residual(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, f.d, nullptr, G->stream);
-        e = coarse_cycle(G, 0, nu1, nu2);
-        if (!e) e = sweep_level(G, 0, nu2);
+        if (tile_level(G, 0)) {
+            tile_phase<double>(G, 0, kTileDown, nu1, nullptr);
+        } else {
+            int e = sweep_level(G, 0, nu1);
+            if (e) return e;
+            launch_residual(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, f.d, nullptr,
+                            G->stream);
+        }
+        int e = coarse_cycle(G, 0, nu1, nu2);
+        return e ? e : fine_up(G, 0, nu2);
+    }
+    if (tile_level(G, l)) {
+        tile_phase<double>(G, l, kTileDown, nu1, nullptr);
+        const int e = vcycle_level(G, l + 1, nu1, nu2);
+        if (!e) tile_phase<double>(G, l, kTileUp, nu2, nullptr);
         return e;
     }
     LevelData &c = G->lev[l + 1];
@@ -941,6 +1196,12 @@ int rs_create_grid(const rs_grid_desc *d, int precision, void *ws_dev, size_t ws
         return fail(RS_EHIP, "hipHostMalloc failed");
     }
     grid_view(G, d, precision, L, (char *)ws_dev, (hipStream_t)stream, bits);
+    void *dev = nullptr;
+    if (hipHostGetDevicePointer(&dev, bits, 0) == hipSuccess && dev &&
+        hipEventCreateWithFlags(&G->norm_ev, hipEventDisableTiming) == hipSuccess)
+        G->host_dev = (unsigned long long *)dev;
+    else
+        (void)hipGetLastError();   // norms by copy
     const char *gv = getenv("RS_GRAPH");
     const bool fused = G->nlev > 0 && G->lev[0].psi_alt;
     if (!(gv && gv[0] == '0') && !fused && hipStreamCreate(&G->cap) != hipSuccess) {
@@ -959,6 +1220,7 @@ void rs_destroy_grid(rs_grid *G)
         if (G->cg[w]) (void)hipGraphExecDestroy(G->cg[w]);
     if (G->cap) (void)hipStreamDestroy(G->cap);
     for (hipEvent_t ev : G->prof_ev) (void)hipEventDestroy(ev);
+    if (G->host_dev) (void)hipEventDestroy(G->norm_ev);
     if (G->host_bits) (void)hipHostFree(G->host_bits);
     delete G;
 }
@@ -1062,6 +1324,7 @@ int rs_begin_step(rs_grid *G, double dt, int order)
     G->step.order = (order == 2 && G->nstep > 0) ? 2 : 1;
     G->step.a = (G->step.order == 1) ? 1.0 / dt : 1.5 / dt;
     LevelData &f = G->lev[0];
+    launch_fill_u64(G->scratch, 1, 0ull, G->stream);   // the norm word (zero between norms)
     launch_setup_kstar(f.geo, G->law, G->step, G->psi_n, G->psi_nm1, G->has_ks ? G->ks : nullptr,
                        f.K, f.psi, G->stream);
     launch_setup_g(f.geo, G->law, G->step, G->psi_n, G->psi_nm1, f.K, f.g, G->stream);
@@ -1180,6 +1443,10 @@ int rs_end_step(rs_grid *G)
     return RS_OK;
 }
 
+namespace {
+constexpr long long kAheadNodes = 1ll << 20;
+}
+
 int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_step_stats *st)
 {
     if (!G || !o) return fail(RS_EINVAL, "null argument");
@@ -1190,8 +1457,34 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     G->nu_coarse = o->nu_coarse;
     int e = rs_begin_step(G, dt, order);
     if (e) return e;
+    const bool mixed = G->precision == RS_MIXED;
+    const int inner = o->mp_inner_cycles > 0 ? o->mp_inner_cycles : 1;
+    // Grids of at most kAheadNodes nodes queue the next cycle's coarse part (it
+    // leaves the fine iterate alone) before they wait for the norm that decides
+    // whether the cycle is run, so that the device does not idle while the host
+    // reads the norm and launches.  The one queued in vain at a step's end costs
+    // what a cycle's coarse part takes, which the gaps of the step's cycles
+    // outweigh on small grids (15 to 25 us each).
+    // Not while profiling (its events would still be running), nor where the
+    // norm comes by a copy that waits for the whole stream.
+    const bool ahead = G->lev[0].geo.N <= kAheadNodes && G->host_dev && !G->prof_on;
+    bool first = true;           // no cycle of the step has run
+    bool queued = false;         // the next correction's head / cycle's coarse part
+    double queued_updates = 0.0; // its pointwise updates, counted once it is used
+    auto queue_head = [&](bool want) {
+        queued = ahead && want && !(o->fmg && first);
+        if (!queued) return;
+        const double u = G->updates;
+        mp_head(G, o->nu1, o->nu2);
+        queued_updates = G->updates - u;
+        G->updates = u;
+    };
     double r;
-    e = fine_norm(G, &r);
+    G->updates = 0.0;
+    e = fine_norm_send(G, nullptr, mixed);   // mixed: with the first correction's start
+    if (e) return e;
+    if (mixed) queue_head(o->max_cycles > 0);
+    e = norm_wait(G, &r);
     if (e) return e;
     double r0 = r;
     int cycles = 0, slow = 0, nh = 0;
@@ -1199,12 +1492,6 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     double hist[64];
     hist[nh++] = r;
     bool stagnated = false;
-    G->updates = 0.0;
-    const bool mixed = G->precision == RS_MIXED;
-    if (mixed) {
-        e = fine_norm(G, &r, nullptr, true);   // defect vector for the first correction
-        if (e) return e;
-    }
     // FP64 V-cycles on grids whose finest level is not part of the
     // one-work-group cycle take the stopping test where the cycle forms the
     // fine defect anyway, after the pre-smoothing: a step ends there, with
@@ -1216,10 +1503,22 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     // before any coarse correction) and the norm after an FMG cycle (which
     // replaces the iterate) start the comparison afresh.
     bool fresh = true;
+    bool in_d = false;   // the iterate is the smoothed one a tiled phase left in d
     while (std::isfinite(r) && r > o->tol_abs && cycles < o->max_cycles) {
         if (test_in_cycle && !(o->fmg && cycles == 0)) {
             double rn;
-            e = presmooth_norm(G, o->nu1, &rn);
+            in_d = tile_level(G, 0);
+            e = presmooth_send(G, o->nu1);
+            if (e) return e;
+            const double u = G->updates;
+            const bool early = ahead && cycles + 1 < o->max_cycles;
+            if (early) {
+                e = coarse_cycle(G, 0, o->nu1, o->nu2);
+                if (e) return e;
+                queued_updates = G->updates - u;
+                G->updates = u;
+            }
+            e = norm_wait(G, &rn);
             if (e) return e;
             ++cycles;
             if (nh < 64) hist[nh++] = rn;
@@ -1235,9 +1534,11 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
             }
             fresh = false;
             if (!(std::isfinite(rn) && rn > o->tol_abs) || cycles >= o->max_cycles) break;
-            e = coarse_cycle(G, 0, o->nu1, o->nu2);
-            if (!e) e = sweep_level(G, 0, o->nu2);
+            if (early) G->updates += queued_updates;
+            else e = coarse_cycle(G, 0, o->nu1, o->nu2);
+            if (!e) e = fine_up(G, 0, o->nu2);
             if (e) return e;
+            in_d = false;
             HIPCALL(hipGetLastError());
             continue;
         }
@@ -1246,14 +1547,20 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
             e = fmg_cycle(G, o->nu1, o->nu2);
             if (e) return e;
         } else if (mixed) {
-            mp_correction(G, o->mp_inner_cycles > 0 ? o->mp_inner_cycles : 1, o->nu1, o->nu2);
+            if (queued) G->updates += queued_updates;
+            else mp_head(G, o->nu1, o->nu2);
+            mp_tail(G, inner, o->nu1, o->nu2);
         } else {
             e = vcycle_level(G, 0, o->nu1, o->nu2);
             if (e) return e;
         }
+        first = false;
         HIPCALL(hipGetLastError());
         double rn;
-        e = fine_norm(G, &rn, nullptr, mixed);
+        e = fine_norm_send(G, nullptr, mixed);
+        if (e) return e;
+        if (mixed) queue_head(cycles + 1 < o->max_cycles);
+        e = norm_wait(G, &rn);
         if (e) return e;
         ++cycles;
         if (nh < 64) hist[nh++] = rn;
@@ -1269,6 +1576,10 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
         }
         if (after_fmg) fresh = true;
     }
+    if (in_d)
+        HIPCALL(hipMemcpyAsync(G->lev[0].psi, G->lev[0].d,
+                               sizeof(double) * (size_t)G->lev[0].geo.N, hipMemcpyDeviceToDevice,
+                               G->stream));
     int status = RS_OK;
     bool stalled = false;
     if (!std::isfinite(r)) status = RS_ENONFINITE;

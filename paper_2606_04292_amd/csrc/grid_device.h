@@ -12,7 +12,7 @@ constexpr int kBY = 4;
 // Maximum over a work-group (NaN wins); the result is valid in thread 0.
 __device__ __forceinline__ double block_max(double v)
 {
-    __shared__ double red[8];
+    __shared__ double red[16];   // up to 1024 threads
     int lane = threadIdx.x + threadIdx.y * blockDim.x;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {

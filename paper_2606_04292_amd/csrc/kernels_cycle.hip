@@ -1,0 +1,92 @@
+// FP64 V-cycles of the small levels in one work-group (cycle_wg.h) and of the
+// mid-size 1-D and 2-D levels in tiles (cycle_tile.h).
+#include "rs_internal.h"
+#include "soil_device.h"
+#include "grid_device.h"
+#include "cycle_wg.h"
+#include "cycle_tile.h"
+
+namespace rs {
+
+namespace {
+
+// The soil table of a layered medium, staged in LDS; null for one law.
+template <int MODEL>
+__device__ __forceinline__ const Law *stage_soils(const Law &L)
+{
+    if constexpr (MODEL == kMulti) {
+        __shared__ Law tab[kMaxSoils];
+        const int *src = (const int *)L.soils;
+        for (int t = threadIdx.x; t < (int)(sizeof(Law) / sizeof(int)) * kMaxSoils;
+             t += blockDim.x)
+            ((int *)tab)[t] = src[t];
+        return tab;   // read after the first barrier of the cycle
+    }
+    return nullptr;
+}
+
+// The V-cycle from a level of at most kTailNodes nodes down and back in one
+// work-group (cycle_wg.h).
+template <int MODEL, bool SINK, int DIM>
+__global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg(WgCycle<double> A, WgMems<double> M,
+                                                            Law L, double a)
+{
+    extern __shared__ double lds64[];
+    const Law *soils = stage_soils<MODEL>(L);
+    typedef WgOp64<MODEL, SINK, DIM> Op;
+    wg_cycle<Op>(A, M, typename Op::Env{L, soils, a}, lds64);
+}
+
+// One tile of a phase of a level (cycle_tile.h).
+template <int MODEL, bool SINK, int DIM>
+__global__ __launch_bounds__(kTileThreads) void k_cycle_tile(TileArgs<double> A, int phase, Law L,
+                                                             double a)
+{
+    extern __shared__ double lds64[];
+    const Law *soils = stage_soils<MODEL>(L);
+    typedef WgOp64<MODEL, SINK, DIM> Op;
+    tile_run<Op>(A, phase, typename Op::Env{L, soils, a}, lds64);
+}
+
+struct CycleWgLaunch {
+    const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; hipStream_t s;
+    template <int MO, bool S, int D>
+    void go()
+    {
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
+        if (bytes > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
+                           law, a);
+    }
+};
+
+struct TileLaunch {
+    const TileArgs<double> &A; int phase, blocks; size_t words; const Law &law; double a;
+    hipStream_t s;
+    template <int MO, bool SK, int D>
+    void go()
+    {
+        const size_t bytes = sizeof(double) * words;
+        if constexpr (D < 3)
+            hipLaunchKernelGGL((k_cycle_tile<MO, SK, D>), dim3(blocks), dim3(kTileThreads), bytes,
+                               s, A, phase, law, a);
+    }
+};
+
+}  // namespace
+
+void launch_tile(const TileArgs<double> &A, int phase, int blocks, size_t words,
+                 const Law &law, double a, hipStream_t s)
+{
+    dispatch<true>(law, A.dim, TileLaunch{A, phase, blocks, words, law, a, s});
+}
+
+void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                     int dim, hipStream_t s)
+{
+    dispatch<true>(law, dim, CycleWgLaunch{A, M, law, a, s});
+}
+
+}  // namespace rs

@@ -17,7 +17,6 @@
 #include "grid_device.h"
 #include "transfer.h"
 #include "cell64.h"
-#include "cycle_wg.h"
 
 namespace rs {
 
@@ -28,6 +27,15 @@ __global__ void k_fill_u64(unsigned long long *p, int n, unsigned long long v)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) p[t] = v;
+}
+
+// The norm word goes to the host's pinned word and is cleared for the next
+// norm (one launch instead of a copy and a fill).
+__global__ void k_norm_out(unsigned long long *word, unsigned long long *host)
+{
+    const unsigned long long v = *word;
+    *word = 0ull;
+    __hip_atomic_store(host, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Reorder an array of one level between the lexicographic order of the C ABI
@@ -961,26 +969,6 @@ __global__ __launch_bounds__(256) void k_sweep_small(Geo g, Law L, Step st, cons
     }
 }
 
-// The V-cycle from a level of at most kTailNodes nodes down and back in one
-// work-group (cycle_wg.h).
-template <int MODEL, bool SINK, int DIM>
-__global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg(WgCycle<double> A, WgMems<double> M,
-                                                            Law L, double a)
-{
-    extern __shared__ double lds64[];
-    const Law *soils = nullptr;
-    if constexpr (MODEL == kMulti) {
-        __shared__ Law tab[kMaxSoils];
-        const int *src = (const int *)L.soils;
-        for (int t = threadIdx.x; t < (int)(sizeof(Law) / sizeof(int)) * kMaxSoils;
-             t += blockDim.x)
-            ((int *)tab)[t] = src[t];
-        soils = tab;
-    }
-    typedef WgOp64<MODEL, SINK, DIM> Op;
-    wg_cycle<Op>(A, M, typename Op::Env{L, soils, a}, lds64);
-}
-
 // ---------------------------------------------------------------------------
 // Defect d = g - N(psi) and its max-norm (step 2 of the FAS algorithm)
 // ---------------------------------------------------------------------------
@@ -1222,6 +1210,11 @@ void launch_relayout_u8(const Geo &g, const unsigned char *src, unsigned char *d
 void launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t s)
 {
     hipLaunchKernelGGL(k_fill_u64, dim3((n + 63) / 64), dim3(64), 0, s, p, n, v);
+}
+
+void launch_norm_out(unsigned long long *word, unsigned long long *host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_norm_out, dim3(1), dim3(1), 0, s, word, host);
 }
 
 void launch_setup_kstar(const Geo &g, const Law &law, const Step &st, const double *psi_n,
@@ -1546,26 +1539,6 @@ void launch_prolong(const Geo &gf, const Geo &gc, const double *psi_c, const dou
                     double *psi_f, hipStream_t s)
 {
     launch_prolong_t<double>(gf, gc, psi_c, psibar_c, psi_f, s);
-}
-
-struct CycleWgLaunch {
-    const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; hipStream_t s;
-    template <int MO, bool S, int D>
-    void go()
-    {
-        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
-        if (bytes > 64 * 1024)
-            (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
-                           law, a);
-    }
-};
-
-void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
-                     int dim, hipStream_t s)
-{
-    dispatch<true>(law, dim, CycleWgLaunch{A, M, law, a, s});
 }
 
 void launch_interp(const Geo &gf, const Geo &gc, const double *psi_c, double *psi_f, hipStream_t s)

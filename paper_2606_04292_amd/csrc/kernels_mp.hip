@@ -12,7 +12,7 @@
 #include "transfer.h"
 #include "soil_mp.h"
 #include "cell32.h"
-#include "cycle_wg.h"
+#include "mp_internal.h"
 
 namespace rs {
 
@@ -249,17 +249,6 @@ __global__ __launch_bounds__(256) void k_apply_delta(long long N, const float *d
     if (t < N) psi64[t] += (double)dl[t];
 }
 
-// The FP32 correction cycle from a level of at most kTailNodes nodes down and
-// back in one work-group (cycle_wg.h).
-template <int MODEL, bool SINK, int DIM>
-__global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg32(WgCycle<float> A, WgMems<float> M,
-                                                              Law32 L, float a)
-{
-    extern __shared__ float lds32[];
-    typedef WgOp32<MODEL, SINK, DIM> Op;
-    wg_cycle<Op>(A, M, typename Op::Env{L, a}, lds32);
-}
-
 unsigned blocks_for(long long N) { return (unsigned)((N + 255) / 256); }
 
 // Two nodes per lane in the FP32 sweeps of levels of at least 2^22 nodes (at
@@ -334,15 +323,6 @@ struct CoarseRhs32Launch {
     }
 };
 
-// dispatch() keys on Law::model / Law::sink; build a Law carrying those two.
-Law dispatch_key(const Law32 &l)
-{
-    Law k{};
-    k.model = l.model;
-    k.sink = l.sink;
-    return k;
-}
-
 }  // namespace
 
 Law32 make_law32(const Law &L)
@@ -394,26 +374,6 @@ void launch_sweep32(const Geo &g, const Law32 &law, float a, const double *beta,
     if (nsweeps <= 0) return;
     dispatch(dispatch_key(law), g.dim,
              Sweep32Launch{g, law, a, beta, lambdaU, K, rhs, pb, dl, nsweeps, s});
-}
-
-struct CycleWg32Launch {
-    const WgCycle<float> &A; const WgMems<float> &M; const Law32 &law; float a; hipStream_t s;
-    template <int MO, bool S, int D>
-    void go()
-    {
-        const size_t bytes = wg_lds_bytes<float, D>(A.g, A.levels);
-        if (bytes > 64 * 1024)
-            (void)hipFuncSetAttribute((const void *)k_cycle_wg32<MO, S, D>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg32<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
-                           M, law, a);
-    }
-};
-
-void launch_cycle_wg32(const WgCycle<float> &A, const WgMems<float> &M, const Law32 &law, float a,
-                       int dim, hipStream_t s)
-{
-    dispatch(dispatch_key(law), dim, CycleWg32Launch{A, M, law, a, s});
 }
 
 void launch_residual32(const Geo &g, const Law32 &law, float a, const double *beta, const float *K,

@@ -7,6 +7,14 @@
 namespace rs {
 
 Law32 make_law32(const Law &L);
+// dispatch() keys on Law::model / Law::sink; a Law carrying those two.
+inline Law dispatch_key(const Law32 &l)
+{
+    Law k{};
+    k.model = l.model;
+    k.sink = l.sink;
+    return k;
+}
 void launch_sweep32(const Geo &g, const Law32 &law, float a, const double *beta, float lambdaU,
                     const float *K, const float *rhs, const float *pb, float *dl, int nsweeps,
                     hipStream_t s);

@@ -90,6 +90,8 @@ constexpr long long kTailNodes = 2049;
 // Kernel launchers (kernels_fp64.hip)
 // ---------------------------------------------------------------------------
 void launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t s);
+// *host (pinned) = *word, *word = 0
+void launch_norm_out(unsigned long long *word, unsigned long long *host, hipStream_t s);
 // Lexicographic (C ABI) order <-> the level's row layout; src and dst must not overlap.
 void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s);
 void launch_relayout_u8(const Geo &g, const unsigned char *src, unsigned char *dst, bool to_level,
