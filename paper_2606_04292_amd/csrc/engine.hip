@@ -126,34 +126,29 @@ __device__ __forceinline__ int find_item(const unsigned *pre, int count, unsigne
     return lo;
 }
 
-// Walk this work-group's contiguous chunk of the list's virtual tiles:
-// body(item, tile-within-item).  flush(item) runs when the chunk leaves an item
-// (and at its end); every call is uniform over the work-group.
-template <typename Body, typename Flush>
-__device__ __forceinline__ void tile_loop(const EList &L, int kind, Body &&body, Flush &&flush)
+// Walk this work-group's contiguous chunk of the list's virtual tiles, item by
+// item: item(it, t0, t1) handles the tiles t0 .. t1 - 1 of item it (uniform over
+// the work-group), so that an item's state is looked at and its records are
+// read once, not once per 256 nodes (an inactive item costs one look).
+template <typename Item>
+__device__ __forceinline__ void tile_loop(const EList &L, int kind, Item &&item)
 {
     const unsigned total = L.total[kind];
     if (total == 0) return;
     const unsigned per = (total + gridDim.x - 1) / gridDim.x;
     const unsigned lb = xcd_block(gridDim.x / 8u);
-    const unsigned v0 = lb * per;
-    const unsigned v1 = min(v0 + per, total);
-    if (v0 >= v1) return;
+    const unsigned v1 = min(lb * per + per, total);
+    unsigned v = lb * per;
+    if (v >= v1) return;
     const unsigned *pre = L.pre[kind];
-    int it = (int)sgpr((unsigned)find_item(pre, L.count, v0));
-    for (unsigned v = v0; v < v1; ++v) {
-        while (v >= pre[it + 1]) {
-            flush(it);
-            ++it;
-        }
-        body(it, v - pre[it]);
+    int it = (int)sgpr((unsigned)find_item(pre, L.count, v));
+    while (v < v1) {
+        const unsigned p0 = sgpr(pre[it]), e = min(v1, sgpr(pre[it + 1]));
+        if (e > v) item(it, v - p0, e - p0);
+        v = e;
+        ++it;
     }
-    flush(it);
 }
-
-struct NoFlush {
-    __device__ void operator()(int) const {}
-};
 
 template <typename Fn>
 __device__ __forceinline__ void law_dim(int model, int dim, Fn &&fn)
@@ -197,107 +192,113 @@ __device__ __forceinline__ Step slot_step(const ESlot &S, const EDyn &D)
 // History shift after a finished step (psi^{n-1} <- psi^n <- psi), first
 // iterate, K* (FP64) and its FP32 copy on every level where the node is a
 // coarse-grid node (injection).
-__global__ __launch_bounds__(256) void e_kstar(const EList *FL, const ESlot *slots, EDyn *dyn,
-                                               const ELevel *levels)
+__global__ __launch_bounds__(256) void e_kstar(const EList *__restrict__ FL,
+                                               const ESlot *__restrict__ slots, EDyn *dyn,
+                                               const ELevel *__restrict__ levels)
 {
     const EList L = *FL;
-    tile_loop(L, 1, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kBegin) return;
         const ESlot &S = slots[s];
-        const EDyn &D = dyn[s];
+        const EDyn D = dyn[s];
         const ELevel &L0 = levels[s * kEngMaxLevels];
-        const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
-        if (t >= (unsigned long long)L0.geo.N) return;
-        int i, j, k;
-        node_ijk(L0.nm, t, i, j, k);
-        if (D.end_prev) {
-            const double p = S.psi[t];
-            S.psi_nm1[t] = S.psi_n[t];
-            S.psi_n[t] = p;
-        }
         const Step st = slot_step(S, D);
-        double p0;
-        const double Kv = kstar_at(L0.geo, S.law, st, S.psi_n, S.psi_nm1, S.law.Ks, i, j, k,
-                                   (long long)t, &p0);
-        S.K[t] = Kv;
-        S.psi[t] = p0;
-        for (int l = 0; l < S.nlev; ++l) {
-            const int m = (1 << l) - 1;
-            if ((i | j | k) & m) break;
-            const ELevel &Lv = levels[s * kEngMaxLevels + l];
-            Lv.K32[lin(Lv.geo, i >> l, j >> l, k >> l)] = (float)Kv;
+        for (unsigned tile = t0; tile < t1; ++tile) {
+            const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+            if (t >= (unsigned long long)L0.geo.N) return;
+            int i, j, k;
+            node_ijk(L0.nm, t, i, j, k);
+            if (D.end_prev) {
+                const double p = S.psi[t];
+                S.psi_nm1[t] = S.psi_n[t];
+                S.psi_n[t] = p;
+            }
+            double p0;
+            const double Kv = kstar_at(L0.geo, S.law, st, S.psi_n, S.psi_nm1, S.law.Ks, i, j, k,
+                                       (long long)t, &p0);
+            S.K[t] = Kv;
+            S.psi[t] = p0;
+            for (int l = 0; l < S.nlev; ++l) {
+                const int m = (1 << l) - 1;
+                if ((i | j | k) & m) break;
+                const ELevel &Lv = levels[s * kEngMaxLevels + l];
+                Lv.K32[lin(Lv.geo, i >> l, j >> l, k >> l)] = (float)Kv;
+            }
         }
-    }, NoFlush{});
+    });
 }
 
-__global__ __launch_bounds__(256) void e_gvec(const EList *FL, const ESlot *slots,
-                                              const EDyn *dyn, const ELevel *levels)
+__global__ __launch_bounds__(256) void e_gvec(const EList *__restrict__ FL,
+                                              const ESlot *__restrict__ slots, const EDyn *dyn,
+                                              const ELevel *__restrict__ levels)
 {
     const EList L = *FL;
-    tile_loop(L, 1, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kBegin) return;
         const ESlot &S = slots[s];
         const ELevel &L0 = levels[s * kEngMaxLevels];
-        const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
-        if (t >= (unsigned long long)L0.geo.N) return;
-        int i, j, k;
-        node_ijk(L0.nm, t, i, j, k);
         const Step st = slot_step(S, dyn[s]);
-        S.g[t] = g_at(L0.geo, S.law, st, S.psi_n, S.psi_nm1, S.K, i, j, k, (long long)t);
-    }, NoFlush{});
+        for (unsigned tile = t0; tile < t1; ++tile) {
+            const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+            if (t >= (unsigned long long)L0.geo.N) return;
+            int i, j, k;
+            node_ijk(L0.nm, t, i, j, k);
+            S.g[t] = g_at(L0.geo, S.law, st, S.psi_n, S.psi_nm1, S.K, i, j, k, (long long)t);
+        }
+    });
 }
 
 // FP64 defect d = g - N(psi) of slots in state `want`: its max-norm into the
 // slot's norm bits, and the start of the next correction: rhs = fl32(d) and
 // delta = 0 on the finest level, base state psi_b = fl32(psi) on every level.
-__global__ __launch_bounds__(256) void e_defect(const EList *FL, const ESlot *slots, EDyn *dyn,
-                                                const ELevel *levels, int want)
+__global__ __launch_bounds__(256) void e_defect(const EList *__restrict__ FL,
+                                                const ESlot *__restrict__ slots, EDyn *dyn,
+                                                const ELevel *__restrict__ levels, int want)
 {
     const EList L = *FL;
-    double v = 0.0, vs = 0.0;
-    tile_loop(L, 1, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != want) return;
         const ESlot &S = slots[s];
         const ELevel &L0 = levels[s * kEngMaxLevels];
-        const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
-        if (t >= (unsigned long long)L0.geo.N) return;
-        int i, j, k;
-        node_ijk(L0.nm, t, i, j, k);
         const double a = dyn[s].a;
-        const double x = S.psi[t];
-        double r = 0.0;
+        double v = 0.0, vs = 0.0;
         law_dim(S.law.model, L0.geo.dim, [&](auto M, auto Dm) {
-            if (dirichlet_t<decltype(Dm)::value>(L0.geo, i, j, k)) return;
-            double terms = 0.0;
-            r = S.g[t] - apply_N_t<decltype(M)::value, false, decltype(Dm)::value, true>(
-                             L0.geo, S.law, a, nullptr, S.K, S.psi, i, j, k, (long long)t, &terms);
-            const double sc = fabs(S.g[t]) + terms;
-            vs = sc > vs ? sc : vs;
+            for (unsigned tile = t0; tile < t1; ++tile) {
+                const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+                if (t >= (unsigned long long)L0.geo.N) break;
+                int i, j, k;
+                node_ijk(L0.nm, t, i, j, k);
+                const double x = S.psi[t];
+                double r = 0.0;
+                if (!dirichlet_t<decltype(Dm)::value>(L0.geo, i, j, k)) {
+                    double terms = 0.0;
+                    r = S.g[t] -
+                        apply_N_t<decltype(M)::value, false, decltype(Dm)::value, true>(
+                            L0.geo, S.law, a, nullptr, S.K, S.psi, i, j, k, (long long)t, &terms);
+                    const double sc = fabs(S.g[t]) + terms;
+                    vs = sc > vs ? sc : vs;
+                }
+                const double ar = fabs(r);
+                v = (ar > v || ar != ar) ? ar : v;
+                L0.rhs[t] = (float)r;
+                L0.dl[t] = 0.0f;
+                for (int l = 0; l < S.nlev; ++l) {
+                    const int m = (1 << l) - 1;
+                    if ((i | j | k) & m) break;
+                    const ELevel &Lv = levels[s * kEngMaxLevels + l];
+                    Lv.pb[lin(Lv.geo, i >> l, j >> l, k >> l)] = (float)x;
+                }
+            }
         });
-        const double ar = fabs(r);
-        v = (ar > v || ar != ar) ? ar : v;
-        L0.rhs[t] = (float)r;
-        L0.dl[t] = 0.0f;
-        for (int l = 0; l < S.nlev; ++l) {
-            const int m = (1 << l) - 1;
-            if ((i | j | k) & m) break;
-            const ELevel &Lv = levels[s * kEngMaxLevels + l];
-            Lv.pb[lin(Lv.geo, i >> l, j >> l, k >> l)] = (float)x;
-        }
-    }, [&](int it) {
-        const int s = L.slot[it];
-        if (dyn[s].state != want) return;   // uniform: same item for the whole group
         const double m = block_max(v);
         if (threadIdx.x == 0) atomicMax(&dyn[s].norm_bits, (unsigned long long)__double_as_longlong(m));
         __syncthreads();
         const double ms = block_max(vs);
         if (threadIdx.x == 0) atomicMax(&dyn[s].scale_bits, (unsigned long long)__double_as_longlong(ms));
         __syncthreads();
-        v = 0.0;
-        vs = 0.0;
     });
 }
 
@@ -386,26 +387,34 @@ __global__ __launch_bounds__(256) void e_control(const ESlot *slots, EDyn *dyn, 
 // FP32 V-cycle of the correction equation, wide levels (slots in ACTIVE)
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void e_sweep32(const EList *DL, const ESlot *slots,
-                                                 const EDyn *dyn, const ELevel *levels, int colour)
+__global__ __launch_bounds__(256) void e_sweep32(const EList *__restrict__ DL,
+                                                 const ESlot *__restrict__ slots,
+                                                 const EDyn *__restrict__ dyn,
+                                                 const ELevel *__restrict__ levels, int colour)
 {
     const EList L = *DL;
-    tile_loop(L, 0, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, 0, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kActive) return;
-        const ESlot &S = slots[s];
-        const ELevel &Lv = levels[s * kEngMaxLevels + L.lev[it]];
-        int i, j, k;
-        if (!colour_ijk(Lv.geo, Lv.cm, (unsigned long long)tile * kTile + threadIdx.x, colour, i,
-                        j, k))
-            return;
+        const ELevel &Lv = levels[s * kEngMaxLevels + (int)sgpr((unsigned)L.lev[it])];
+        const Law32 law = slots[s].law32;
+        const Geo geo = Lv.geo;
+        const ColourMap cm = Lv.cm;
+        const float *K32 = Lv.K32, *rhs = Lv.rhs, *pb = Lv.pb;
+        float *dl = Lv.dl;
         const float a = (float)dyn[s].a;
-        law_dim(S.law.model, Lv.geo.dim, [&](auto M, auto Dm) {
-            if (dirichlet_t<decltype(Dm)::value>(Lv.geo, i, j, k)) return;
-            ngs_cell32<decltype(M)::value, false, decltype(Dm)::value, true>(
-                Lv.geo, S.law32, a, nullptr, 0.0f, Lv.K32, Lv.rhs, Lv.pb, Lv.dl, i, j, k, colour);
+        law_dim(law.model, geo.dim, [&](auto M, auto Dm) {
+            for (unsigned tile = t0; tile < t1; ++tile) {
+                int i, j, k;
+                if (!colour_ijk(geo, cm, (unsigned long long)tile * kTile + threadIdx.x, colour, i,
+                                j, k))
+                    continue;
+                if (dirichlet_t<decltype(Dm)::value>(geo, i, j, k)) continue;
+                ngs_cell32<decltype(M)::value, false, decltype(Dm)::value, true>(
+                    geo, law, a, nullptr, 0.0f, K32, rhs, pb, dl, i, j, k, colour);
+            }
         });
-    }, NoFlush{});
+    });
 }
 
 __device__ __forceinline__ void resid32_node(const ESlot &S, float a, const ELevel &Lv,
@@ -460,30 +469,32 @@ __device__ __forceinline__ void prolong32_node(const ELevel &F, const ELevel &C,
 
 // op 0: inner defect on level d; 1: restriction d -> d+1; 2: FAS right-hand
 // side on d+1; 3: prolongation d+1 -> d.
-__global__ __launch_bounds__(256) void e_transfer32(const EList *DL, const ESlot *slots,
-                                                    const EDyn *dyn, const ELevel *levels, int op)
+__global__ __launch_bounds__(256) void e_transfer32(const EList *__restrict__ DL,
+                                                    const ESlot *__restrict__ slots,
+                                                    const EDyn *__restrict__ dyn,
+                                                    const ELevel *__restrict__ levels, int op)
 {
     const EList L = *DL;
     const int kind = (op == 1 || op == 2) ? 2 : 1;
-    tile_loop(L, kind, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, kind, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kActive) return;
         const ESlot &S = slots[s];
-        const ELevel &F = levels[s * kEngMaxLevels + L.lev[it]];
-        const ELevel &C = levels[s * kEngMaxLevels + L.lev[it] + 1];
-        const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+        const int lev = (int)sgpr((unsigned)L.lev[it]);
+        const ELevel &F = levels[s * kEngMaxLevels + lev];
+        const ELevel &C = levels[s * kEngMaxLevels + lev + 1];
         const float a = (float)dyn[s].a;
         const Arrs AF = arrs_of(F), AC = arrs_of(C);
-        if (kind == 1) {
-            if (t >= (unsigned long long)F.geo.N) return;
+        const unsigned long long N = (unsigned long long)(kind == 1 ? F.geo.N : C.geo.N);
+        for (unsigned tile = t0; tile < t1; ++tile) {
+            const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+            if (t >= N) return;
             if (op == 0) resid32_node(S, a, F, AF, t);
+            else if (op == 1) restrict32_node(F, C, AF, AC, t);
+            else if (op == 2) crhs32_node(S, a, C, AC, t);
             else prolong32_node(F, C, AF, AC, t);
-        } else {
-            if (t >= (unsigned long long)C.geo.N) return;
-            if (op == 1) restrict32_node(F, C, AF, AC, t);
-            else crhs32_node(S, a, C, AC, t);
         }
-    }, NoFlush{});
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -607,18 +618,24 @@ __global__ __launch_bounds__(1024) void e_tail(const EList *TL, const ESlot *slo
 }
 
 // psi += delta in FP64 on the finest level (delta is 0 at Dirichlet nodes).
-__global__ __launch_bounds__(256) void e_apply(const EList *FL, const ESlot *slots,
-                                               const EDyn *dyn, const ELevel *levels)
+__global__ __launch_bounds__(256) void e_apply(const EList *__restrict__ FL,
+                                               const ESlot *__restrict__ slots,
+                                               const EDyn *__restrict__ dyn,
+                                               const ELevel *__restrict__ levels)
 {
     const EList L = *FL;
-    tile_loop(L, 1, [&](int it, unsigned tile) {
-        const int s = L.slot[it];
+    tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
+        const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kActive) return;
         const ELevel &L0 = levels[s * kEngMaxLevels];
-        const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
-        if (t >= (unsigned long long)L0.geo.N) return;
-        slots[s].psi[t] += (double)L0.dl[t];
-    }, NoFlush{});
+        double *psi = slots[s].psi;
+        const float *dl = L0.dl;
+        for (unsigned tile = t0; tile < t1; ++tile) {
+            const unsigned long long t = (unsigned long long)tile * kTile + threadIdx.x;
+            if (t >= (unsigned long long)L0.geo.N) return;
+            psi[t] += (double)dl[t];
+        }
+    });
 }
 
 // ---------------------------------------------------------------------------
