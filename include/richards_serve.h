@@ -50,7 +50,9 @@ typedef struct rs_engine_opts {
     size_t struct_size;   /* sizeof(rs_engine_opts) */
     int max_slots;        /* requests resident at once, 1..4096 */
     int max_wide_levels;  /* levels above tail_nodes per request, 0..8 (graph depth) */
-    int tail_nodes;       /* levels of at most this many nodes run in one work-group, >= 27 */
+    int tail_nodes;       /* levels of at most this many nodes run in one work-group, >= 27
+                             (a level too large for that work-group's LDS cycle runs as a
+                             wide one while the request has fewer than max_wide_levels) */
     int nu1, nu2, nu_coarse;
     int max_corrections;  /* per step; a step needing more fails with RS_ENOTCONV */
     double tol_abs;       /* step done when ||g - N(psi)||_inf <= max(tol_abs, tol_rel * r0) */
@@ -62,7 +64,8 @@ typedef struct rs_engine_opts {
                              a|theta|, xi|psi_i|, m_ij (|psi_i| + |psi_j|)); a stall
                              above that fails the request with RS_ENOTCONV */
     int rounds_per_tick;  /* correction rounds queued per rs_engine_tick, >= 1 */
-    int use_graph;        /* 1: replay a captured HIP graph per round; 0: plain launches */
+    int use_graph;        /* 1: replay a captured HIP graph per round (one per wide depth,
+                             captured when first used); 0: plain launches */
 } rs_engine_opts;
 
 typedef struct rs_request_stats {

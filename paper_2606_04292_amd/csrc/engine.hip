@@ -45,18 +45,23 @@
 #include "cell64.h"
 #include "cell32.h"
 #include "mp_internal.h"
+#include "cycle_wg.h"
 #include "host_common.h"
 
 namespace rs {
 namespace {
 
 constexpr int kTile = 256;
-constexpr int kWideGroups = 2048;   // work-groups of every batched multi-group kernel
+// Work-groups of every batched multi-group kernel: a group's start (list, item,
+// records) takes longer than a tile, so few groups with longer chunks win: 128
+// requests of the stream with 1024 / 2048 / 4096 groups 160 / 167 / 185 ms.
+constexpr int kWideGroups = 1024;
 constexpr int kEngMaxLevels = 12;   // up to 2^11 + 1 nodes on the shortest axis
 constexpr int kMaxSlots = 4096;
 constexpr int kMaxWide = 8;
-constexpr int kTailThreads = 1024;        // work-group of the small-level cycle
-constexpr size_t kTailLdsMax = 152 * 1024;  // LDS the small-level cycle may use
+// LDS of the small-level cycle: enough for a 2049-node column (five boxes per
+// level and the defect: 91 KB).
+constexpr size_t kTailLdsMax = 96 * 1024;
 
 enum : int { kEmpty = 0, kBegin = 1, kActive = 2, kFinished = 3, kFailed = 4 };
 
@@ -85,7 +90,8 @@ struct ESlot {
     double *psi, *psi_n, *psi_nm1, *K, *g;
     double tol_abs, tol_rel;
     int stagnation, max_corr;
-    int tail_lds;   // small levels fit in the tail's LDS
+    int wg_top;     // first level of the one-work-group cycle (nlev: none)
+    WgGeo wg_geo;
 };
 
 struct EDyn {
@@ -114,16 +120,40 @@ struct EList {
 __device__ __forceinline__ unsigned sgpr(unsigned v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Index of the item whose tile range holds virtual tile v (pre is ascending,
-// pre[0] = 0, pre[count] = total).
+// pre[0] = 0, pre[count] = total): the lanes of a wave compare 64 entries at a
+// time (a binary search is seven dependent loads for 128 requests).
 __device__ __forceinline__ int find_item(const unsigned *pre, int count, unsigned v)
 {
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (pre[mid] <= v) lo = mid;
-        else hi = mid - 1;
+    const int lane = (int)(threadIdx.x & 63u);
+    int n = 0;
+    for (int q = 0; q < count; q += 64) {
+        const bool le = q + lane < count && pre[q + lane] <= v;
+        n += __popcll(__builtin_amdgcn_ballot_w64(le));
     }
-    return lo;
+    return n - 1;
+}
+
+// The slots in BEGIN at the start of a round and the prefix sums of their fine
+// tiles, made on the device (their number is known only there): the set-up
+// kernels spread the few slots' tiles over all work-groups.
+struct EBegin {
+    int count;
+    unsigned total[3];   // [1]: fine tiles, as in EList
+    int slot[kMaxSlots];
+    unsigned pre[kMaxSlots + 1];
+};
+
+__device__ __forceinline__ EList begin_list(const EBegin *B)
+{
+    EList L;
+    L.count = B->count;
+    L.total[0] = L.total[2] = 0;
+    L.total[1] = B->total[1];
+    L.slot = B->slot;
+    L.lev = nullptr;
+    L.pre[0] = L.pre[2] = nullptr;
+    L.pre[1] = B->pre;
+    return L;
 }
 
 // Walk this work-group's contiguous chunk of the list's virtual tiles, item by
@@ -189,14 +219,69 @@ __device__ __forceinline__ Step slot_step(const ESlot &S, const EDyn &D)
 // Step set-up (slots in BEGIN)
 // ---------------------------------------------------------------------------
 
+// Builds the list of the slots in BEGIN, in slot order (one work-group).
+__global__ __launch_bounds__(1024) void e_begin(const EDyn *dyn, const ELevel *levels, int nslots,
+                                                EBegin *B)
+{
+    __shared__ int wc[16];
+    __shared__ unsigned wt[16];
+    int base = 0;
+    unsigned tbase = 0;
+    for (int s0 = 0; s0 < nslots; s0 += 1024) {
+        const int s = s0 + (int)threadIdx.x;
+        const bool on = s < nslots && dyn[s].state == kBegin;
+        const unsigned tiles =
+            on ? (unsigned)((levels[s * kEngMaxLevels].geo.N + kTile - 1) / kTile) : 0u;
+        // inclusive scans over the wave, then over the waves
+        const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+        int c = on ? 1 : 0;
+        unsigned t = tiles;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int cu = __shfl_up(c, d);
+            const unsigned tu = __shfl_up(t, d);
+            if (lane >= d) {
+                c += cu;
+                t += tu;
+            }
+        }
+        if (lane == 63) {
+            wc[wave] = c;
+            wt[wave] = t;
+        }
+        __syncthreads();
+        int co = base, call = 0;
+        unsigned to = tbase, tall = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) {
+                co += wc[w];
+                to += wt[w];
+            }
+            call += wc[w];
+            tall += wt[w];
+        }
+        if (on) {
+            B->slot[co + c - 1] = s;
+            B->pre[co + c - 1] = to + t - tiles;
+        }
+        base += call;
+        tbase += tall;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        B->pre[base] = tbase;
+        B->count = base;
+        B->total[1] = tbase;
+    }
+}
+
 // History shift after a finished step (psi^{n-1} <- psi^n <- psi), first
 // iterate, K* (FP64) and its FP32 copy on every level where the node is a
 // coarse-grid node (injection).
-__global__ __launch_bounds__(256) void e_kstar(const EList *__restrict__ FL,
+__global__ __launch_bounds__(256) void e_kstar(const EBegin *__restrict__ FL,
                                                const ESlot *__restrict__ slots, EDyn *dyn,
                                                const ELevel *__restrict__ levels)
 {
-    const EList L = *FL;
+    const EList L = begin_list(FL);
     tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
         const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kBegin) return;
@@ -229,11 +314,11 @@ __global__ __launch_bounds__(256) void e_kstar(const EList *__restrict__ FL,
     });
 }
 
-__global__ __launch_bounds__(256) void e_gvec(const EList *__restrict__ FL,
+__global__ __launch_bounds__(256) void e_gvec(const EBegin *__restrict__ FL,
                                               const ESlot *__restrict__ slots, const EDyn *dyn,
                                               const ELevel *__restrict__ levels)
 {
-    const EList L = *FL;
+    const EList L = begin_list(FL);
     tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
         const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != kBegin) return;
@@ -254,10 +339,11 @@ __global__ __launch_bounds__(256) void e_gvec(const EList *__restrict__ FL,
 // slot's norm bits, and the start of the next correction: rhs = fl32(d) and
 // delta = 0 on the finest level, base state psi_b = fl32(psi) on every level.
 __global__ __launch_bounds__(256) void e_defect(const EList *__restrict__ FL,
+                                                const EBegin *__restrict__ BL,
                                                 const ESlot *__restrict__ slots, EDyn *dyn,
                                                 const ELevel *__restrict__ levels, int want)
 {
-    const EList L = *FL;
+    const EList L = want == kBegin ? begin_list(BL) : *FL;
     tile_loop(L, 1, [&](int it, unsigned t0, unsigned t1) {
         const int s = (int)sgpr((unsigned)L.slot[it]);
         if (dyn[s].state != want) return;
@@ -501,8 +587,7 @@ __global__ __launch_bounds__(256) void e_transfer32(const EList *__restrict__ DL
 // Small levels: one work-group per slot runs the cycle from level `wide` down
 // to the coarsest and back, with work-group barriers between the steps.  Its
 // helpers are inlined: as calls they took a stack frame and the call ABI's
-// register budget (248 VGPRs against 127), and the array pointers of the LDS
-// variant lost their address space (flat instead of LDS loads).
+// register budget (248 VGPRs against 127).
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ void tail_sweeps(const ESlot &S, float a, const ELevel &Lv,
@@ -531,16 +616,40 @@ __device__ __forceinline__ void tail_sweeps(const ESlot &S, float a, const ELeve
     }
 }
 
-// The V-cycle from level top down to the coarsest and back, one work-group;
-// arrs(l) gives the arrays of level l the cycle works on.
-template <typename Arr>
-__device__ __forceinline__ void tail_cycle(const ESlot &S, float a, const ELevel *LV, int top,
-                                           int last, int nu1, int nu2, int nuc, Arr &&arrs)
+// Level memory of a request for the one-work-group cycle.
+struct SlotMems {
+    const ELevel *lv;   // its top level
+    __device__ __forceinline__ WgMem<float> operator()(int s) const
+    {
+        return WgMem<float>{lv[s].K32, lv[s].pb, nullptr, nullptr, 0.0};
+    }
+};
+
+// One work-group per request runs its small levels: those that fit the one-
+// work-group cycle (cycle_wg.h) in LDS, the ones above them (a 65^2 or 17^3
+// level under the default tail_nodes) from memory.  The largest requests of a
+// round set the launch's time: 372 us on memory-layout LDS arrays with every
+// node's record read anew in each pass, 128 requests of the stream.
+__global__ __launch_bounds__(kWgMaxThreads) void e_tail(const EList *__restrict__ TL,
+                                                        const ESlot *__restrict__ slots,
+                                                        const EDyn *__restrict__ dyn,
+                                                        const ELevel *__restrict__ levels, int nu1,
+                                                        int nu2, int nuc)
 {
-    for (int l = top; l < last; ++l) {
+    extern __shared__ float smem[];
+    const int b = blockIdx.x;
+    if (b >= TL->count) return;
+    const int s = (int)sgpr((unsigned)TL->slot[b]);
+    if (dyn[s].state != kActive) return;
+    const ESlot &S = slots[s];
+    const ELevel *LV = levels + s * kEngMaxLevels;
+    const float a = (float)dyn[s].a;
+    const int last = S.nlev - 1, top = S.wide, wg = S.wg_top;
+    for (int l = top; l < wg; ++l) {
         const ELevel &F = LV[l], &C = LV[l + 1];
-        const Arrs AF = arrs(l), AC = arrs(l + 1);
-        tail_sweeps(S, a, F, AF, nu1, false);
+        const Arrs AF = arrs_of(F), AC = arrs_of(C);
+        tail_sweeps(S, a, F, AF, l == last ? nuc : nu1, l == last);
+        if (l == last) break;
         for (unsigned long long t = threadIdx.x; t < (unsigned long long)F.geo.N; t += blockDim.x)
             resid32_node(S, a, F, AF, t);
         __syncthreads();
@@ -551,70 +660,24 @@ __device__ __forceinline__ void tail_cycle(const ESlot &S, float a, const ELevel
             crhs32_node(S, a, C, AC, t);
         __syncthreads();
     }
-    tail_sweeps(S, a, LV[last], arrs(last), nuc, true);
-    for (int l = last - 1; l >= top; --l) {
+    if (wg <= last) {
+        const WgCycle<float> A{S.wg_geo, last - wg + 1, nu1, nu2, nuc, LV[wg].dl, LV[wg].rhs};
+        const SlotMems M{LV + wg};
+        const Law32 law = S.law32;
+        law_dim(law.model, LV[0].geo.dim, [&](auto Mo, auto Dm) {
+            typedef WgOp32<decltype(Mo)::value, false, decltype(Dm)::value> Op;
+            wg_cycle<Op>(A, M, typename Op::Env{law, a}, smem);
+        });
+        __syncthreads();
+    }
+    for (int l = min(wg, last) - 1; l >= top; --l) {
         const ELevel &F = LV[l], &C = LV[l + 1];
-        const Arrs AF = arrs(l), AC = arrs(l + 1);
+        const Arrs AF = arrs_of(F), AC = arrs_of(C);
         for (unsigned long long t = threadIdx.x; t < (unsigned long long)F.geo.N; t += blockDim.x)
             prolong32_node(F, C, AF, AC, t);
         __syncthreads();
         tail_sweeps(S, a, F, AF, nu2, false);
     }
-}
-
-// Arrays of level l of a request whose small levels live in LDS: levels
-// top..last one after another, each as dl, K32, rhs, r, dbar, pb (N_l floats).
-__device__ __forceinline__ Arrs lds_arrs(const ELevel *LV, int top, int l, float *smem)
-{
-    size_t off = 0;
-    for (int q = top; q < l; ++q) off += 6 * (size_t)LV[q].geo.N;
-    const size_t N = (size_t)LV[l].geo.N;
-    float *p = smem + off;
-    return Arrs{p, p + N, p + 2 * N, p + 3 * N, p + 4 * N, p + 5 * N};
-}
-
-__device__ __forceinline__ void block_copy(float *dst, const float *src, long long n)
-{
-    for (long long t = threadIdx.x; t < n; t += blockDim.x) dst[t] = src[t];
-}
-
-// One work-group per request runs its small levels.  A request whose small
-// levels fit in LDS (ESlot::tail_lds) works there: K32 and psi_b of every small
-// level and delta, rhs of the top one are staged in, the cycle runs on LDS,
-// and delta of the top level is written back (the wide levels' prolongation
-// reads it).
-__global__ __launch_bounds__(1024) void e_tail(const EList *TL, const ESlot *slots,
-                                              const EDyn *dyn, const ELevel *levels, int nu1,
-                                              int nu2, int nuc)
-{
-    extern __shared__ float smem[];
-    const int b = blockIdx.x;
-    if (b >= TL->count) return;
-    const int s = TL->slot[b];
-    if (dyn[s].state != kActive) return;
-    const ESlot &S = slots[s];
-    const ELevel *LV = levels + s * kEngMaxLevels;
-    const float a = (float)dyn[s].a;
-    const int top = S.wide, last = S.nlev - 1;
-    if (!S.tail_lds) {
-        tail_cycle(S, a, LV, top, last, nu1, nu2, nuc, [&](int l) { return arrs_of(LV[l]); });
-        return;
-    }
-    for (int l = top; l <= last; ++l) {
-        const Arrs A = lds_arrs(LV, top, l, smem);
-        const long long N = LV[l].geo.N;
-        block_copy(A.K32, LV[l].K32, N);
-        block_copy(A.pb, LV[l].pb, N);
-        if (l == top) {
-            block_copy(A.dl, LV[l].dl, N);
-            block_copy(A.rhs, LV[l].rhs, N);
-        }
-    }
-    __syncthreads();
-    tail_cycle(S, a, LV, top, last, nu1, nu2, nuc,
-               [&](int l) { return lds_arrs(LV, top, l, smem); });
-    const Arrs T = lds_arrs(LV, top, top, smem);
-    block_copy(LV[top].dl, T.dl, LV[top].geo.N);
 }
 
 // psi += delta in FP64 on the finest level (delta is 0 at Dirichlet nodes).
@@ -692,7 +755,7 @@ private:
 // Byte layout of the control region (device arena start, mirrored in pinned
 // host memory).
 struct CtrlLayout {
-    size_t slots, dyn, levels, lists, arrays, total;
+    size_t slots, dyn, levels, lists, begin, arrays, total;
     int nlists;
     size_t list_stride;   // bytes of one list's arrays
 };
@@ -707,6 +770,7 @@ CtrlLayout ctrl_layout(const rs_engine_opts &o)
     c.dyn = off;    off = align_up(off + sizeof(EDyn) * S);
     c.levels = off; off = align_up(off + sizeof(ELevel) * S * kEngMaxLevels);
     c.lists = off;  off = align_up(off + sizeof(EList) * c.nlists);
+    c.begin = off;  off = align_up(off + sizeof(EBegin));
     c.list_stride = align_up(sizeof(int) * 2 * S + sizeof(unsigned) * 3 * (S + 1));
     c.arrays = off; off = align_up(off + c.list_stride * c.nlists);
     c.total = off;
@@ -742,6 +806,10 @@ int plan_request(const rs_engine_opts &o, const rs_grid_desc *d, ReqPlan *p)
     if (p->wide >= p->nlev)
         return fail(RS_EINVAL, "coarsest level has %lld nodes, above tail_nodes %d",
                      p->geo[p->nlev - 1].N, o.tail_nodes);
+    // a small level that does not fit the one-work-group cycle's LDS boxes runs
+    // as a wide one where the engine has a depth left for it
+    while (p->wide < o.max_wide_levels && p->wide + 1 < p->nlev && !wg_level_fits(p->geo[p->wide]))
+        p->wide += 1;
     if (p->wide > o.max_wide_levels)
         return fail(RS_EINVAL, "request has %d levels above tail_nodes; the engine runs %d",
                     p->wide, o.max_wide_levels);
@@ -797,6 +865,7 @@ struct rs_engine {
     EDyn *d_dyn, *h_dyn;
     ELevel *d_levels, *h_levels;
     EList *d_lists, *h_lists;
+    EBegin *d_begin;
     Arena arena;
     size_t data_base;   // arena offset where request data starts
     std::vector<int> ticket;          // per slot, -1 if free
@@ -807,9 +876,7 @@ struct rs_engine {
     int next_ticket;
     int hi_slot;                      // one past the highest slot ever used
     bool lists_dirty;
-    hipGraph_t graph;
-    hipGraphExec_t exec;
-    bool graph_ready;
+    hipGraphExec_t exec[kMaxWide + 1];   // the round with that many wide depths
     size_t tail_lds_bytes;            // dynamic LDS of the small-level cycle
 };
 
@@ -819,6 +886,15 @@ template <typename T>
 T *dev_at(rs_engine *E, size_t off) { return reinterpret_cast<T *>(E->base + off); }
 template <typename T>
 T *host_at(rs_engine *E, size_t off) { return reinterpret_cast<T *>(E->host + off); }
+
+// LDS of the one-work-group cycle over the given levels from top down.
+size_t tail_lds(const Geo &top, int levels)
+{
+    const WgGeo w = wg_geo(top);
+    return top.dim == 1 ? wg_lds_bytes<float, 1>(w, levels)
+                        : (top.dim == 2 ? wg_lds_bytes<float, 2>(w, levels)
+                                        : wg_lds_bytes<float, 3>(w, levels));
+}
 
 // Rebuild the fine, per-depth and tail lists from the resident slots and copy
 // them to the device.
@@ -876,8 +952,9 @@ int upload_lists(rs_engine *E)
     return RS_OK;
 }
 
-// One correction round for every resident slot (the captured sequence).
-void enqueue_round(rs_engine *E)
+// One correction round for every resident slot, of which none has more than
+// `depths` wide levels (the captured sequence).
+void enqueue_round(rs_engine *E, int depths)
 {
     const rs_engine_opts &o = E->o;
     const int W = o.max_wide_levels;
@@ -886,13 +963,15 @@ void enqueue_round(rs_engine *E)
     const EList *fine = E->d_lists;
     const EList *tail = E->d_lists + W + 1;
     const int ctl_groups = (o.max_slots + 255) / 256;
-    hipLaunchKernelGGL(e_kstar, wg, blk, 0, s, fine, E->d_slots, E->d_dyn, E->d_levels);
-    hipLaunchKernelGGL(e_gvec, wg, blk, 0, s, fine, E->d_slots, E->d_dyn, E->d_levels);
-    hipLaunchKernelGGL(e_defect, wg, blk, 0, s, fine, E->d_slots, E->d_dyn, E->d_levels,
+    EBegin *bl = E->d_begin;
+    hipLaunchKernelGGL(e_begin, dim3(1), dim3(1024), 0, s, E->d_dyn, E->d_levels, o.max_slots, bl);
+    hipLaunchKernelGGL(e_kstar, wg, blk, 0, s, bl, E->d_slots, E->d_dyn, E->d_levels);
+    hipLaunchKernelGGL(e_gvec, wg, blk, 0, s, bl, E->d_slots, E->d_dyn, E->d_levels);
+    hipLaunchKernelGGL(e_defect, wg, blk, 0, s, fine, bl, E->d_slots, E->d_dyn, E->d_levels,
                        (int)kBegin);
     hipLaunchKernelGGL(e_control, dim3(ctl_groups), blk, 0, s, E->d_slots, E->d_dyn,
                        o.max_slots, 0);
-    for (int d = 0; d < W; ++d) {
+    for (int d = 0; d < depths; ++d) {
         const EList *dl = E->d_lists + 1 + d;
         for (int sw = 0; sw < o.nu1; ++sw)
             for (int c = 0; c < 2; ++c)
@@ -902,9 +981,9 @@ void enqueue_round(rs_engine *E)
             hipLaunchKernelGGL(e_transfer32, wg, blk, 0, s, dl, E->d_slots, E->d_dyn,
                                E->d_levels, op);
     }
-    hipLaunchKernelGGL(e_tail, dim3(o.max_slots), dim3(kTailThreads), E->tail_lds_bytes, s, tail,
+    hipLaunchKernelGGL(e_tail, dim3(o.max_slots), dim3(kWgMaxThreads), E->tail_lds_bytes, s, tail,
                        E->d_slots, E->d_dyn, E->d_levels, o.nu1, o.nu2, o.nu_coarse);
-    for (int d = W - 1; d >= 0; --d) {
+    for (int d = depths - 1; d >= 0; --d) {
         const EList *dl = E->d_lists + 1 + d;
         hipLaunchKernelGGL(e_transfer32, wg, blk, 0, s, dl, E->d_slots, E->d_dyn, E->d_levels, 3);
         for (int sw = 0; sw < o.nu2; ++sw)
@@ -913,22 +992,25 @@ void enqueue_round(rs_engine *E)
                                    E->d_levels, c);
     }
     hipLaunchKernelGGL(e_apply, wg, blk, 0, s, fine, E->d_slots, E->d_dyn, E->d_levels);
-    hipLaunchKernelGGL(e_defect, wg, blk, 0, s, fine, E->d_slots, E->d_dyn, E->d_levels,
+    hipLaunchKernelGGL(e_defect, wg, blk, 0, s, fine, bl, E->d_slots, E->d_dyn, E->d_levels,
                        (int)kActive);
     hipLaunchKernelGGL(e_control, dim3(ctl_groups), blk, 0, s, E->d_slots, E->d_dyn,
                        o.max_slots, 1);
 }
 
-int capture_graph(rs_engine *E)
+int capture_graph(rs_engine *E, int depths)
 {
     HIPCALL(hipStreamBeginCapture(E->stream, hipStreamCaptureModeThreadLocal));
-    enqueue_round(E);
+    enqueue_round(E, depths);
     hipGraph_t g = nullptr;
     hipError_t e1 = hipStreamEndCapture(E->stream, &g);
     if (e1 != hipSuccess) return fail(RS_EHIP, "graph capture: %s", hipGetErrorString(e1));
-    E->graph = g;
-    HIPCALL(hipGraphInstantiate(&E->exec, g, nullptr, nullptr, 0));
-    E->graph_ready = true;
+    e1 = hipGraphInstantiate(&E->exec[depths], g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (e1 != hipSuccess) {
+        E->exec[depths] = nullptr;
+        return fail(RS_EHIP, "graph instantiation: %s", hipGetErrorString(e1));
+    }
     return RS_OK;
 }
 
@@ -995,9 +1077,7 @@ int rs_engine_create(const rs_engine_opts *o, void *arena_dev, size_t arena_byte
     E->bytes = arena_bytes;
     E->cl = cl;
     E->host = nullptr;
-    E->graph = nullptr;
-    E->exec = nullptr;
-    E->graph_ready = false;
+    for (hipGraphExec_t &x : E->exec) x = nullptr;
     E->tail_lds_bytes = 0;
     if (hipGetDevice(&E->device) != hipSuccess ||
         hipHostMalloc((void **)&E->host, cl.total, hipHostMallocDefault) != hipSuccess) {
@@ -1024,6 +1104,7 @@ int rs_engine_create(const rs_engine_opts *o, void *arena_dev, size_t arena_byte
     E->h_levels = host_at<ELevel>(E, cl.levels);
     E->d_lists = dev_at<EList>(E, cl.lists);
     E->h_lists = host_at<EList>(E, cl.lists);
+    E->d_begin = dev_at<EBegin>(E, cl.begin);
     E->data_base = cl.total;
     E->arena.reset(arena_bytes - cl.total);
     const int S = o->max_slots;
@@ -1043,13 +1124,12 @@ int rs_engine_create(const rs_engine_opts *o, void *arena_dev, size_t arena_byte
     }
     E->lists_dirty = true;
     e = upload_lists(E);
-    if (e == RS_OK && o->use_graph) e = capture_graph(E);
     if (e == RS_OK && hipStreamSynchronize(E->stream) != hipSuccess)
         e = fail(RS_EHIP, "engine set-up");
     if (e) {
         (void)hipStreamSynchronize(E->stream);   // pending copies read the pinned mirror
-        if (E->exec) (void)hipGraphExecDestroy(E->exec);
-        if (E->graph) (void)hipGraphDestroy(E->graph);
+        for (hipGraphExec_t x : E->exec)
+            if (x) (void)hipGraphExecDestroy(x);
         (void)hipHostFree(E->host);
         delete E;
         return e;
@@ -1103,11 +1183,13 @@ int rs_engine_submit(rs_engine *E, const rs_grid_desc *d, const rs_constitutive 
     S.tol_rel = E->o.tol_rel;
     S.stagnation = E->o.stagnation;
     S.max_corr = E->o.max_corrections;
-    {
-        size_t tb = 0;
-        for (int l = P.wide; l < P.nlev; ++l) tb += 6 * sizeof(float) * (size_t)P.geo[l].N;
-        S.tail_lds = (E->tail_lds_bytes > 0 && tb <= E->tail_lds_bytes) ? 1 : 0;
-    }
+    S.wg_top = P.nlev;
+    if (E->tail_lds_bytes > 0)
+        while (S.wg_top > P.wide && P.nlev - (S.wg_top - 1) <= kWgMaxLev &&
+               wg_level_fits(P.geo[S.wg_top - 1]) &&
+               tail_lds(P.geo[S.wg_top - 1], P.nlev - (S.wg_top - 1)) <= E->tail_lds_bytes)
+            --S.wg_top;
+    if (S.wg_top < P.nlev) S.wg_geo = wg_geo(P.geo[S.wg_top]);
     for (int l = 0; l < P.nlev; ++l) {
         ELevel &Lv = E->h_levels[s * kEngMaxLevels + l];
         memset(&Lv, 0, sizeof Lv);
@@ -1153,12 +1235,17 @@ int rs_engine_tick(rs_engine *E, int *done, int max_done, int *n_done, int *n_ac
         int e = upload_lists(E);
         if (e) return e;
     }
-    bool any = false;
-    for (int s = 0; s < E->hi_slot; ++s) any = any || E->ticket[s] >= 0;
-    if (any) {
+    int depths = -1;   // most wide levels of a resident request
+    for (int s = 0; s < E->hi_slot; ++s)
+        if (E->ticket[s] >= 0) depths = std::max(depths, E->plans[s].wide);
+    if (depths >= 0) {
+        if (E->o.use_graph && !E->exec[depths]) {   // on first use of that depth
+            int e = capture_graph(E, depths);
+            if (e) return e;
+        }
         for (int r = 0; r < E->o.rounds_per_tick; ++r) {
-            if (E->graph_ready) HIPCALL(hipGraphLaunch(E->exec, E->stream));
-            else enqueue_round(E);
+            if (E->exec[depths]) HIPCALL(hipGraphLaunch(E->exec[depths], E->stream));
+            else enqueue_round(E, depths);
         }
         HIPCALL(hipGetLastError());
         if (E->hi_slot > 0)
@@ -1228,8 +1315,8 @@ void rs_engine_destroy(rs_engine *E)
 {
     if (!E) return;
     (void)hipStreamSynchronize(E->stream);
-    if (E->exec) (void)hipGraphExecDestroy(E->exec);
-    if (E->graph) (void)hipGraphDestroy(E->graph);
+    for (hipGraphExec_t x : E->exec)
+        if (x) (void)hipGraphExecDestroy(x);
     if (E->host) (void)hipHostFree(E->host);
     delete E;
 }
