@@ -156,6 +156,8 @@ struct Layout {
 };
 
 constexpr int kScratchWords = 64;
+// Pinned host words: the scratch words' mirror, then a whole-grid solve's report.
+constexpr int kHostWords = kScratchWords + (int)((sizeof(WgSolveOut) + 7) / 8);
 
 // Every array is placed with at least kPad zeroed bytes before and after it
 // (the workspace is cleared at creation): the single-grid stencils load the
@@ -634,6 +636,7 @@ void sweep32_level(rs_grid *G, int l, int nsweeps)
 int vcycle_level(rs_grid *G, int l, int nu1, int nu2);
 void vcycle32_level(rs_grid *G, int l, int nu1, int nu2);
 int coarse_cycle(rs_grid *G, int which, int nu1, int nu2);
+double wg_updates(const rs_grid *G, int l, int nu1, int nu2);
 
 // ---------------------------------------------------------------------------
 // Tiled levels (cycle_tile.h)
@@ -936,11 +939,7 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
             M.lv[q - l] = WgMem<float>{G->lev[q].K32, G->lev[q].pb32, G->lev[q].beta, nullptr,
                                        G->lev[q].lambdaU};
         launch_cycle_wg32(A, M, G->law32, a, G->desc.dim, G->stream);
-        for (int q = l; q < G->nlev - 1; ++q)
-            G->updates += (double)(nu1 + nu2) * (double)G->lev[q].unknowns;
-        // the coarsest level's loop may stop after its first sweep (4-ulp exit):
-        // counted as one sweep
-        G->updates += (double)G->lev[G->nlev - 1].unknowns;
+        G->updates += wg_updates(G, l, nu1, nu2);
         return;
     }
     if (l == G->nlev - 1) {
@@ -1001,22 +1000,35 @@ void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
     mp_tail(G, inner, nu1, nu2);
 }
 
+// The FP64 one-work-group cycle from level l down.
+void wg_args(const rs_grid *G, int l, int nu1, int nu2, WgCycle<double> *A, WgMems<double> *M)
+{
+    const LevelData &f = G->lev[l];
+    *A = WgCycle<double>{wg_geo(f.geo), G->nlev - l, nu1, nu2, G->nu_coarse, f.psi, f.g};
+    for (int q = l; q < G->nlev; ++q)
+        M->lv[q - l] = WgMem<double>{G->lev[q].K, nullptr, G->lev[q].beta, G->lev[q].geo.soil,
+                                     G->lev[q].lambdaU};
+}
+
+// Pointwise updates of a cycle of the one-work-group levels from l down (the
+// coarsest level's loop may stop after its first sweep: counted as one).
+double wg_updates(const rs_grid *G, int l, int nu1, int nu2)
+{
+    double u = (double)G->lev[G->nlev - 1].unknowns;
+    for (int q = l; q < G->nlev - 1; ++q) u += (double)(nu1 + nu2) * (double)G->lev[q].unknowns;
+    return u;
+}
+
 int vcycle_level(rs_grid *G, int l, int nu1, int nu2)
 {
     LevelData &f = G->lev[l];
     if (l >= G->tail_top && l < G->nlev - 1) {
         // the rest of the cycle on small levels: one work-group, one launch
-        WgCycle<double> A{wg_geo(f.geo), G->nlev - l, nu1, nu2, G->nu_coarse, f.psi, f.g};
+        WgCycle<double> A;
         WgMems<double> M;
-        for (int q = l; q < G->nlev; ++q)
-            M.lv[q - l] = WgMem<double>{G->lev[q].K, nullptr, G->lev[q].beta,
-                                        G->lev[q].geo.soil, G->lev[q].lambdaU};
+        wg_args(G, l, nu1, nu2, &A, &M);
         launch_cycle_wg(A, M, G->law, G->step.a, G->desc.dim, G->stream);
-        for (int q = l; q < G->nlev - 1; ++q)
-            G->updates += (double)(nu1 + nu2) * (double)G->lev[q].unknowns;
-        // the coarsest level's loop may stop after its first sweep (4-ulp exit):
-        // counted as one sweep
-        G->updates += (double)G->lev[G->nlev - 1].unknowns;
+        G->updates += wg_updates(G, l, nu1, nu2);
         return RS_OK;
     }
     if (l == G->nlev - 1) return sweep_level(G, l, G->nu_coarse);
@@ -1190,7 +1202,7 @@ int rs_create_grid(const rs_grid_desc *d, int precision, void *ws_dev, size_t ws
     rs_grid *G = new (std::nothrow) rs_grid();
     if (!G) return fail(RS_ENOMEM, "host allocation failed");
     unsigned long long *bits = nullptr;
-    if (hipHostMalloc((void **)&bits, kScratchWords * sizeof(unsigned long long),
+    if (hipHostMalloc((void **)&bits, kHostWords * sizeof(unsigned long long),
                       hipHostMallocDefault) != hipSuccess) {
         delete G;
         return fail(RS_EHIP, "hipHostMalloc failed");
@@ -1293,8 +1305,7 @@ int rs_set_state(rs_grid *G, const double *psi_n, const double *psi_nm1, int nst
 {
     if (!G || !psi_n) return fail(RS_EINVAL, "null argument");
     const Geo &g0 = G->lev[0].geo;
-    launch_relayout(g0, psi_n, G->psi_n, true, G->stream);
-    launch_relayout(g0, psi_nm1 ? psi_nm1 : psi_n, G->psi_nm1, true, G->stream);
+    launch_relayout(g0, psi_n, G->psi_n, true, G->stream, psi_nm1 ? psi_nm1 : psi_n, G->psi_nm1);
     HIPCALL(hipGetLastError());
     G->nstep = nstep;
     G->t = t;
@@ -1306,8 +1317,8 @@ int rs_get_state(const rs_grid *G, double *psi_n, double *psi_nm1, int *nstep, d
 {
     if (!G) return fail(RS_EINVAL, "null grid");
     const Geo &g0 = G->lev[0].geo;
-    if (psi_n) launch_relayout(g0, G->psi_n, psi_n, false, G->stream);
-    if (psi_nm1) launch_relayout(g0, G->psi_nm1, psi_nm1, false, G->stream);
+    if (psi_n) launch_relayout(g0, G->psi_n, psi_n, false, G->stream, G->psi_nm1, psi_nm1);
+    else if (psi_nm1) launch_relayout(g0, G->psi_nm1, psi_nm1, false, G->stream);
     HIPCALL(hipGetLastError());
     if (nstep) *nstep = G->nstep;
     if (t) *t = G->t;
@@ -1324,19 +1335,27 @@ int rs_begin_step(rs_grid *G, double dt, int order)
     G->step.order = (order == 2 && G->nstep > 0) ? 2 : 1;
     G->step.a = (G->step.order == 1) ? 1.0 / dt : 1.5 / dt;
     LevelData &f = G->lev[0];
-    launch_fill_u64(G->scratch, 1, 0ull, G->stream);   // the norm word (zero between norms)
     launch_setup_kstar(f.geo, G->law, G->step, G->psi_n, G->psi_nm1, G->has_ks ? G->ks : nullptr,
                        f.K, f.psi, G->stream);
     launch_setup_g(f.geo, G->law, G->step, G->psi_n, G->psi_nm1, f.K, f.g, G->stream);
-    for (int l = 1; l < G->nlev; ++l) {
-        if (G->coarse_k == RS_COARSE_FW)
+    const bool mixed = G->precision == RS_MIXED;
+    if (G->coarse_k == RS_COARSE_FW) {
+        for (int l = 1; l < G->nlev; ++l)
             launch_fw_coarse(G->lev[l].geo, G->lev[l - 1].geo, G->lev[l - 1].K, G->lev[l].K, G->stream);
-        else
-            launch_inject(G->lev[l].geo, G->lev[l - 1].geo, G->lev[l - 1].K, G->lev[l].K, G->stream);
+        if (mixed)
+            for (int l = 0; l < G->nlev; ++l)
+                launch_to_f32(G->lev[l].geo.N, G->lev[l].K, G->lev[l].K32, G->stream);
+    } else {
+        Geo geo[kMaxLevels];
+        double *K[kMaxLevels];
+        float *K32[kMaxLevels];
+        for (int l = 0; l < G->nlev; ++l) {
+            geo[l] = G->lev[l].geo;
+            K[l] = G->lev[l].K;
+            K32[l] = mixed ? G->lev[l].K32 : nullptr;
+        }
+        launch_inject_k(geo, K, K32, G->nlev, G->stream);
     }
-    if (G->precision == RS_MIXED)
-        for (int l = 0; l < G->nlev; ++l)
-            launch_to_f32(G->lev[l].geo.N, G->lev[l].K, G->lev[l].K32, G->stream);
     HIPCALL(hipGetLastError());
     if (G->law.kappa_rule == kKappaRemark) {
         launch_fill_u64(G->scratch + 1, G->nlev, 0ull, G->stream);
@@ -1479,19 +1498,25 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
         queued_updates = G->updates - u;
         G->updates = u;
     };
-    double r;
-    G->updates = 0.0;
-    e = fine_norm_send(G, nullptr, mixed);   // mixed: with the first correction's start
-    if (e) return e;
-    if (mixed) queue_head(o->max_cycles > 0);
-    e = norm_wait(G, &r);
-    if (e) return e;
-    double r0 = r;
+    // FP64 grids that fit one work-group run their cycles and the stopping test
+    // in it, kWgSolveCycles to a launch.
+    const bool whole = !mixed && G->nlev > 1 && G->tail_top == 0 && G->host_dev;
+    double r = 0.0, r0 = 0.0, best = 0.0;
     int cycles = 0, slow = 0, nh = 0;
-    double best = r;
     double hist[64];
-    hist[nh++] = r;
     bool stagnated = false;
+    G->updates = 0.0;
+    const bool first_in_solve = whole && !o->fmg;
+    if (!first_in_solve) {
+        e = fine_norm_send(G, nullptr, mixed);   // mixed: with the first correction's start
+        if (e) return e;
+        if (mixed) queue_head(o->max_cycles > 0);
+        e = norm_wait(G, &r);
+        if (e) return e;
+        r0 = r;
+        best = r;
+        hist[nh++] = r;
+    }
     // FP64 V-cycles on grids whose finest level is not part of the
     // one-work-group cycle take the stopping test where the cycle forms the
     // fine defect anyway, after the pre-smoothing: a step ends there, with
@@ -1504,7 +1529,36 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     // replaces the iterate) start the comparison afresh.
     bool fresh = true;
     bool in_d = false;   // the iterate is the smoothed one a tiled phase left in d
-    while (std::isfinite(r) && r > o->tol_abs && cycles < o->max_cycles) {
+    bool first_norm = first_in_solve;
+    while (first_norm || (std::isfinite(r) && r > o->tol_abs && cycles < o->max_cycles)) {
+        if (whole && !(o->fmg && cycles == 0)) {
+            WgCycle<double> A;
+            WgMems<double> M;
+            wg_args(G, 0, o->nu1, o->nu2, &A, &M);
+            const int left = o->max_cycles - cycles;
+            const WgSolve S{o->tol_abs, best, slow, o->stagnation,
+                            left < kWgSolveCycles ? left : kWgSolveCycles, first_norm ? 1 : 0};
+            launch_solve_wg(A, M, G->law, G->step.a, G->desc.dim, S,
+                            (WgSolveOut *)(G->host_dev + kScratchWords), G->stream);
+            HIPCALL(hipGetLastError());
+            HIPCALL(hipStreamSynchronize(G->stream));
+            WgSolveOut out;
+            memcpy(&out, G->host_bits + kScratchWords, sizeof out);
+            if (first_norm) {
+                r0 = out.hist[0];
+                hist[nh++] = r0;
+                first_norm = false;
+            }
+            for (int q = 1; q <= out.cycles && nh < 64; ++q) hist[nh++] = out.hist[q];
+            r = out.r;
+            best = out.best;
+            slow = out.slow;
+            cycles += out.cycles;
+            G->updates += out.cycles * wg_updates(G, 0, o->nu1, o->nu2);
+            stagnated = out.stagnated != 0;
+            if (stagnated) break;
+            continue;
+        }
         if (test_in_cycle && !(o->fmg && cycles == 0)) {
             double rn;
             in_d = tile_level(G, 0);

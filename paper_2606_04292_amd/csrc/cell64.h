@@ -58,10 +58,11 @@ __device__ __forceinline__ double g_at(const Geo &g, const Law &L, const Step &s
     // gravity (M z)_i: only faces along the vertical axis, z_i - z_j = -side h
     double Ki = K[idx];
     double mz = 0.0;
-    const int v = g.vert;
-    for_each_nb(g, c, idx, [&](long long jn, double cf, int l, int side) {
-        if (l == v) mz += cf * (Ki + K[jn]) * (-side * g.h[v]);
-    });
+    const int v = g.vert, cv = c[v];
+    const double cf = ((cv == 0 || cv == g.n[v] - 1) ? 1.0 : 0.5) * g.ih2[v];
+    if (cv > 0) mz += cf * (Ki + K[v == 0 ? xnb(g, i, idx, -1) : idx - g.stride[v]]) * g.h[v];
+    if (cv < g.n[v] - 1)
+        mz += cf * (Ki + K[v == 0 ? xnb(g, i, idx, 1) : idx + g.stride[v]]) * -g.h[v];
     double gi = H + L.xi * ps - mz;
     if (c[v] == 0 && g.bc[2 * v] == kBcFreedrain) {
         double iw = 2.0;   // bottom node: half control volume

@@ -35,6 +35,8 @@
 namespace rs {
 
 constexpr int kWgMaxLev = 12;        // levels of one cycle (2049 nodes on the shortest axis)
+// Cycles of one launch of the whole-grid solve (a few milliseconds at most).
+constexpr int kWgSolveCycles = 60;
 // Three waves per SIMD, so a lane may hold 168 registers (2-D and 3-D levels
 // take one node per thread and colour; with two the 3-D kernels spilled).
 constexpr int kWgMaxThreads = 768;
@@ -343,14 +345,17 @@ __device__ __forceinline__ void wg_sync()
 // sweeps, defect and its restriction to level s + 1; the coarsest level has
 // only the sweeps.  Up: the coarser level's correction, sweeps.  A level that
 // is left for good holds its correction x - bar in bar (the top level's x
-// goes back to memory).  The LDS reads of a step are issued together, ahead of
+// goes back to memory unless the cycle repeats, and with norm set its defect's
+// max-norm into *norm).  norm_only: just that norm, of the top level's iterate
+// as it is.  The LDS reads of a step are issued together, ahead of
 // its arithmetic (a read takes about 70 cycles: waited for one by one, the 54
 // taps of a 3-D restriction took 6000).
 template <class Op, int S, bool WAVE>
 __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                                          const WgMem<typename Op::T> &M,
                                          const typename Op::Env &e, int s, bool up, int nthreads,
-                                         typename Op::T *lds, int off, typename Op::T *dbox)
+                                         typename Op::T *lds, int off, typename Op::T *dbox,
+                                         double *norm = nullptr, bool norm_only = false)
 {
     typedef typename Op::T T;
     constexpr int DIM = Op::DIM, NQ = 2 * DIM;
@@ -498,7 +503,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
         }
     }
     if (up) wg_sync<WAVE>();
-    const int n = last ? A.nuc : (up ? A.nu2 : A.nu1);
+    const int n = norm_only ? 0 : (last ? A.nuc : (up ? A.nu2 : A.nu1));
     for (int sw = 0; sw < n; ++sw) {
         bool changed = false;
 #pragma unroll
@@ -530,7 +535,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
             }
         }
     }
-    if (!up && !last) {
+    if (!up && !last && !norm_only) {
         // defect (0 at Dirichlet nodes), then its full weighting and the iterate's
         {
             T xn[2][S][NQ];
@@ -611,6 +616,31 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
             for (int u = 0; u < S; ++u)
                 if (has[col][u]) B.bar[nd[col][u].p] = nd[col][u].x - B.bar[nd[col][u].p];
         wg_sync<WAVE>();
+    } else if (norm) {
+        double m = 0.0;
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                typename Op::Node &q = nd[col][u];
+                T lin1;
+                const T loc = Op::local(e, q, q.x, lin1);
+                T md = T(0);
+#pragma unroll
+                for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - B.x[q.p + so[t]]);
+                const double r = on[col][u] ? fabs((double)(q.g - (loc + (lin1 + md)))) : 0.0;
+                m = (r > m || r != r) ? r : m;
+            }
+        if (WAVE) {
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) {
+                const double o = __shfl_xor(m, d);
+                m = (o > m || o != o) ? o : m;
+            }
+        } else {
+            m = block_max(m);
+        }
+        if (tid == 0) *norm = m;
     } else {
 #pragma unroll
         for (int col = 0; col < 2; ++col)
@@ -624,12 +654,10 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
     }
 }
 
-// The cycle: down and up over the levels, two nodes per thread and colour on
-// 1-D levels of more than kWgMaxThreads nodes per colour, one wave from the
-// first level of at most 64 nodes per colour.
+// The levels' LDS boxes from memory; returns the defect box.
 template <class Op, class Mem>
-__device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const Mem &mem,
-                                         const typename Op::Env &e, typename Op::T *lds)
+__device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T> &A,
+                                                   const Mem &mem, typename Op::T *lds)
 {
     typedef typename Op::T T;
     constexpr int DIM = Op::DIM;
@@ -693,7 +721,45 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
         off += W * v.size;
     }
     __syncthreads();
-    off = 0;
+    return dbox;
+}
+
+// One visit, in the mode of its level: two nodes per thread and colour on 1-D
+// levels of more than kWgMaxThreads nodes per colour, one wave from the first
+// level of at most 64 nodes per colour (wave: the last visit was of that kind).
+template <class Op, class Mem>
+__device__ __forceinline__ void wg_visit_mode(const WgCycle<typename Op::T> &A, const Mem &mem,
+                                              const typename Op::Env &e, int s, bool up,
+                                              bool &wave, typename Op::T *lds, int off,
+                                              typename Op::T *dbox, double *norm, bool norm_only)
+{
+    constexpr int DIM = Op::DIM;
+    const int nthreads = blockDim.x;
+    const int slots = (wg_level<DIM>(A.g, s).N + 1) / 2;
+    if (slots <= 64) {
+        wave = true;
+        if (threadIdx.x < 64)
+            wg_visit<Op, 1, true>(A, mem(s), e, s, up, 64, lds, off, dbox, norm, norm_only);
+        return;
+    }
+    if (wave) __syncthreads();   // the other waves join again
+    wave = false;
+    if (slots <= nthreads)
+        wg_visit<Op, 1, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox, norm, norm_only);
+    else if constexpr (DIM == 1)
+        wg_visit<Op, 2, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox, norm, norm_only);
+}
+
+// The cycle: down and up over the levels.
+template <class Op, class Mem>
+__device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const Mem &mem,
+                                         const typename Op::Env &e, typename Op::T *lds)
+{
+    typedef typename Op::T T;
+    constexpr int DIM = Op::DIM;
+    constexpr int W = sizeof(T) == 4 ? 5 : 4;   // boxes per level
+    T *dbox = wg_load<Op>(A, mem, lds);
+    int off = 0;
     const int visits = 2 * A.levels - 1;
     bool wave = false;
     for (int q = 0; q < visits; ++q) {
@@ -701,18 +767,96 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
         const int s = up ? visits - 1 - q : q;
         const int sz = wg_level<DIM>(A.g, s).size;
         if (up) off -= W * sz;
-        const int slots = (wg_level<DIM>(A.g, s).N + 1) / 2;
-        if (slots <= 64) {
-            wave = true;
-            if (tid < 64) wg_visit<Op, 1, true>(A, mem(s), e, s, up, 64, lds, off, dbox);
-        } else {
-            if (wave) __syncthreads();   // the other waves join again
-            wave = false;
-            if (slots <= nthreads) wg_visit<Op, 1, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox);
-            else if constexpr (DIM == 1)
-                wg_visit<Op, 2, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox);
-        }
+        wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, nullptr, false);
         if (!up && s + 1 < A.levels) off += W * sz;
+    }
+}
+
+// Cycles of a whole grid in one work-group until the step's stopping test ends
+// them (the test of rs_bdf_step: the norm after each cycle at most tol, not
+// finite, or two cycles in a row without a new minimum), at most `most` of
+// them, with the iterate in LDS throughout.
+struct WgSolve {
+    double tol, best;
+    int slow, stagnation, most;
+    int first;    // 1: the norm of the iterate as it is comes first (hist[0])
+};
+
+// What it reports: the norm after each cycle, behind the first norm.
+struct WgSolveOut {
+    double r, best;
+    int cycles, slow, stagnated, pad;
+    double hist[kWgSolveCycles + 1];
+};
+
+template <class Op, class Mem>
+__device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const Mem &mem,
+                                         const typename Op::Env &e, typename Op::T *lds,
+                                         const WgSolve &S, WgSolveOut *out)
+{
+    typedef typename Op::T T;
+    constexpr int DIM = Op::DIM;
+    constexpr int W = sizeof(T) == 4 ? 5 : 4;
+    __shared__ double norm;
+    T *dbox = wg_load<Op>(A, mem, lds);
+    const int visits = 2 * A.levels - 1;
+    bool wave = false, stagnated = false;
+    double best = S.best, r = 0.0;
+    int slow = S.slow, cycles = 0, off = 0;
+    // one loop over all visits (the visit's code appears once per mode): q = -1
+    // is the norm of the iterate as it is
+    int q = S.first ? -1 : 0;
+    while (true) {
+        const bool up = q >= A.levels;
+        const int s = q < 0 ? 0 : (up ? visits - 1 - q : q);
+        const int sz = wg_level<DIM>(A.g, s).size;
+        if (up) off -= W * sz;
+        const bool end = q < 0 || q == visits - 1;
+        wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, end ? &norm : nullptr, q < 0);
+        if (!end) {
+            if (!up && s + 1 < A.levels) off += W * sz;
+            ++q;
+            continue;
+        }
+        __syncthreads();
+        wave = false;
+        r = norm;
+        const bool finite = fabs(r) <= 1.7976931348623157e308;
+        if (q < 0) {
+            best = r;
+            if (threadIdx.x == 0) out->hist[0] = r;
+        } else {
+            ++cycles;
+            if (threadIdx.x == 0) out->hist[cycles] = r;
+            if (S.stagnation) {
+                if (r < best) {
+                    best = r;
+                    slow = 0;
+                } else if (++slow >= 2) {
+                    stagnated = true;
+                }
+            }
+        }
+        if (stagnated || !(finite && r > S.tol) || cycles >= S.most) break;
+        q = 0;
+        off = 0;
+        __syncthreads();
+    }
+    // the iterate back to memory
+    const WgLevel<DIM> v = wg_level<DIM>(A.g, 0);
+    const WgBox<T, DIM> B = wg_box<T, DIM>(lds, 0, v);
+    for (int t = threadIdx.x; t < v.N; t += blockDim.x) {
+        int c[3];
+        wg_ijk<DIM>(v, t, c);
+        A.x[wg_mem<DIM>(A.g, v, c)] = B.x[wg_pos<DIM>(v, c)];
+    }
+    if (threadIdx.x == 0) {
+        out->r = r;
+        out->best = best;
+        out->cycles = cycles;
+        out->slow = slow;
+        out->stagnated = stagnated ? 1 : 0;
+        __threadfence_system();
     }
 }
 
@@ -735,7 +879,10 @@ inline int wg_threads(const WgGeo &g, int dim)
     return (t + 63) / 64 * 64;
 }
 
-// Launchers (kernels_fp64.hip, kernels_mp.hip): one cycle as one work-group.
+// Launchers (kernels_cycle.hip, kernels_cycle32.hip): one cycle, or the cycles
+// of a step, as one work-group.
+void launch_solve_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                     int dim, const WgSolve &S, WgSolveOut *out, hipStream_t s);
 void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
                      int dim, hipStream_t s);
 void launch_cycle_wg32(const WgCycle<float> &A, const WgMems<float> &M, const Law32 &law, float a,

@@ -37,6 +37,18 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg(WgCycle<double> A, W
     wg_cycle<Op>(A, M, typename Op::Env{L, soils, a}, lds64);
 }
 
+// The cycles of a step on a grid whose finest level fits one work-group.
+template <int MODEL, bool SINK, int DIM>
+__global__ __launch_bounds__(kWgMaxThreads) void k_solve_wg(WgCycle<double> A, WgMems<double> M,
+                                                            Law L, double a, WgSolve S,
+                                                            WgSolveOut *out)
+{
+    extern __shared__ double lds64[];
+    const Law *soils = stage_soils<MODEL>(L);
+    typedef WgOp64<MODEL, SINK, DIM> Op;
+    wg_solve<Op>(A, M, typename Op::Env{L, soils, a}, lds64, S, out);
+}
+
 // One tile of a phase of a level (cycle_tile.h).
 template <int MODEL, bool SINK, int DIM>
 __global__ __launch_bounds__(kTileThreads) void k_cycle_tile(TileArgs<double> A, int phase, Law L,
@@ -62,6 +74,21 @@ struct CycleWgLaunch {
     }
 };
 
+struct SolveWgLaunch {
+    const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; const WgSolve &S;
+    WgSolveOut *out; hipStream_t s;
+    template <int MO, bool SK, int D>
+    void go()
+    {
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
+        if (bytes > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)k_solve_wg<MO, SK, D>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        hipLaunchKernelGGL((k_solve_wg<MO, SK, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
+                           M, law, a, S, out);
+    }
+};
+
 struct TileLaunch {
     const TileArgs<double> &A; int phase, blocks; size_t words; const Law &law; double a;
     hipStream_t s;
@@ -81,6 +108,12 @@ void launch_tile(const TileArgs<double> &A, int phase, int blocks, size_t words,
                  const Law &law, double a, hipStream_t s)
 {
     dispatch<true>(law, A.dim, TileLaunch{A, phase, blocks, words, law, a, s});
+}
+
+void launch_solve_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                     int dim, const WgSolve &S, WgSolveOut *out, hipStream_t s)
+{
+    dispatch<true>(law, dim, SolveWgLaunch{A, M, law, a, S, out, s});
 }
 
 void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,

@@ -40,18 +40,20 @@ __global__ void k_norm_out(unsigned long long *word, unsigned long long *host)
 
 // Reorder an array of one level between the lexicographic order of the C ABI
 // and the level's row layout (Geo::xs): to_level: dst[layout index of node t]
-// = src[t], t the lexicographic index; else dst[t] = src[layout index].
+// = src[t], t the lexicographic index; else dst[t] = src[layout index].  The same for
+// a second pair of arrays unless dst2 is null.
 template <typename T>
 __global__ __launch_bounds__(256) void k_relayout(Geo g, const T *src, T *dst, int to_level,
-                                                  FastDiv d0)
+                                                  FastDiv d0, const T *src2, T *dst2)
 {
     const unsigned long long t = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (unsigned long long)g.N) return;
     const unsigned row = udiv((unsigned)t, d0);
     const int i = (int)(t - (unsigned long long)row * (unsigned)g.n[0]);
     const long long m = (long long)row * g.n[0] + xpos(g, i);
-    if (to_level) dst[m] = src[t];
-    else dst[t] = src[m];
+    const long long from = to_level ? (long long)t : m, to = to_level ? m : (long long)t;
+    dst[to] = src[from];
+    if (dst2) dst2[to] = src2[from];
 }
 
 // ---------------------------------------------------------------------------
@@ -1190,15 +1192,17 @@ void launch_root_beta(int nlev, const int *nvert, const double *hvert, double *c
 }
 
 template <typename T>
-static void relayout_t(const Geo &g, const T *src, T *dst, bool to_level, hipStream_t s)
+static void relayout_t(const Geo &g, const T *src, T *dst, bool to_level, hipStream_t s,
+                       const T *src2 = nullptr, T *dst2 = nullptr)
 {
     hipLaunchKernelGGL(k_relayout<T>, dim3((unsigned)((g.N + 255) / 256)), dim3(256), 0, s, g, src,
-                       dst, to_level ? 1 : 0, make_fastdiv((unsigned)g.n[0]));
+                       dst, to_level ? 1 : 0, make_fastdiv((unsigned)g.n[0]), src2, dst2);
 }
 
-void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s)
+void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s,
+                     const double *src2, double *dst2)
 {
-    relayout_t<double>(g, src, dst, to_level, s);
+    relayout_t<double>(g, src, dst, to_level, s, src2, dst2);
 }
 
 void launch_relayout_u8(const Geo &g, const unsigned char *src, unsigned char *dst, bool to_level,

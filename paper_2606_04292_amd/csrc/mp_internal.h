@@ -30,6 +30,9 @@ void launch_prolong32(const Geo &gf, const Geo &gc, const float *dl_c, const flo
 // psi_b of levels 1 .. nlev-1 by injection from level 0, in one launch
 // (geo[l] and pb[l]: level l's geometry and FP32 base state).
 void launch_inject_base32(const Geo *geo, float *const *pb, int nlev, hipStream_t s);
+// K* of levels 1 .. nlev-1 by injection from level 0 and, where K32[l] is set,
+// its FP32 copy on every level, in one launch.
+void launch_inject_k(const Geo *geo, double *const *K, float *const *K32, int nlev, hipStream_t s);
 void launch_to_f32(long long N, const double *src, float *dst, hipStream_t s);
 void launch_apply_delta(long long N, const float *dl, double *psi64, hipStream_t s);
 

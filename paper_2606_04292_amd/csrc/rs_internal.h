@@ -93,7 +93,9 @@ void launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStre
 // *host (pinned) = *word, *word = 0
 void launch_norm_out(unsigned long long *word, unsigned long long *host, hipStream_t s);
 // Lexicographic (C ABI) order <-> the level's row layout; src and dst must not overlap.
-void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s);
+// src2, dst2: a second pair of arrays of the same level, in the same launch (dst2 null: none).
+void launch_relayout(const Geo &g, const double *src, double *dst, bool to_level, hipStream_t s,
+                     const double *src2 = nullptr, double *dst2 = nullptr);
 void launch_relayout_u8(const Geo &g, const unsigned char *src, unsigned char *dst, bool to_level,
                         hipStream_t s);
 void launch_setup_kstar(const Geo &g, const Law &law, const Step &st, const double *psi_n,

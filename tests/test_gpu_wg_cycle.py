@@ -79,14 +79,16 @@ def test_vcycles_match_the_oracle(name):
     G.close()
 
 
+@pytest.mark.parametrize("precision", [rsl.RS_FP64, rsl.RS_MIXED], ids=["fp64", "mixed"])
 @pytest.mark.parametrize("name", sorted(n for n in CASES if not n.startswith("soils")))
-def test_mixed_steps_match_the_oracle(name):
+def test_steps_match_the_oracle(name, precision):
+    """FP64: the step's cycles and its stopping test run in one launch on these grids."""
     w = CASES[name]
     if w.law.kappa_rule == W.KAPPA_REMARK:
         w = dataclasses.replace(w, steps=1)
-    say("wg cycle, mixed", name)
+    say("wg cycle, steps", name, precision)
     S = oracle.Solver(w, oracle.ORDER_RB)
-    G = rsl.Grid(w, precision=rsl.RS_MIXED)
+    G = rsl.Grid(w, precision=precision)
     opts = rsl.solve_opts(w.nu1, w.nu2, w.nu_coarse, max_cycles=FLOOR_CYCLES, tol_abs=0.0,
                           stagnation=1)
     for step in range(w.steps):
@@ -98,4 +100,26 @@ def test_mixed_steps_match_the_oracle(name):
         e = rel(np_(G.get_state()[0]), S.get(oracle.FIELD_PSI_N))
         say("  step", step, "corrections", st.cycles, "rel", e)
         assert e <= TOL_CONV, (name, step, e)
+    G.close()
+
+
+@pytest.mark.parametrize("name", ["1d_127_slots", "3d_5x5x5", "soils_33"])
+def test_solve_in_several_launches(name):
+    """More cycles than one launch of the whole-grid solve runs, without a tolerance to reach:
+    as many cycles as asked for, the reported norms are those of the iterates."""
+    w = CASES[name]
+    G = rsl.Grid(w)
+    code, st = G.bdf_step(opts=rsl.solve_opts(w.nu1, w.nu2, 32, max_cycles=130, tol_abs=0.0))
+    if code == rsl.RS_OK:       # a defect of exactly zero ends the step
+        assert st.res == 0.0
+    else:
+        assert code == rsl.RS_ENOTCONV and st.cycles == 130 and st.n_hist == 64
+    G.set_state(G.torch.as_tensor(w.psi0))
+    G.begin_step()
+    r0 = G.residual_norm()
+    assert abs(st.res0 - r0) <= 1e-12 * r0 and st.res_hist[0] == st.res0
+    G.vcycle()
+    r1 = G.residual_norm()
+    say("several launches", name, st.cycles, st.res, "first cycle", st.res_hist[1], r1)
+    assert abs(st.res_hist[1] - r1) <= 1e-9 * r0
     G.close()
