@@ -193,6 +193,24 @@ struct WgOp64 {
         PowState ps;   // power terms of the last evaluation of this visit
         int p, soil;
     };
+    // Values per node that carry the power terms from one visit to the next: for
+    // the vGM law, whose fresh evaluation is two logarithms and two exponentials
+    // (a 257-node column's step 1.93 -> 1.81 ms; with the Haverkamp law or
+    // per-node soils the cycle got slower by 5 %)
+    static constexpr int kKept = MODEL == kVgm ? 3 : 0;
+    static __device__ __forceinline__ void take(Node &nd, const T *kept, int stride)
+    {
+        if constexpr (kKept > 0)
+            nd.ps = pow_kept(kept[nd.p], kept[stride + nd.p], kept[2 * stride + nd.p]);
+    }
+    static __device__ __forceinline__ void keep(const Node &nd, T *kept, int stride)
+    {
+        if constexpr (kKept > 0) {
+            kept[nd.p] = nd.ps.ok ? nd.ps.h : 0.0;
+            kept[stride + nd.p] = nd.ps.q;
+            kept[2 * stride + nd.p] = nd.ps.se;
+        }
+    }
     static __device__ __forceinline__ void coefficients(const Env &e, Node &nd, T mii)
     {
         nd.c = e.L.xi + nd.kap + mii;
@@ -218,7 +236,8 @@ struct WgOp64 {
             const Law &Ls = e.soils[nd.soil];
             return local_solve_soil_ic<SINK, 0>(Ls, e.a, nd.b, nd.c, nd.ic, f, nd.x, nd.ps);
         } else {
-            return local_solve_ic<MODEL, SINK, 0>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x, nd.ps);
+            return local_solve_ic<MODEL, SINK, 0, false, true>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x,
+                                                               nd.ps);
         }
     }
     // moved by more than 4 ulp
@@ -244,6 +263,9 @@ struct WgOp32 {
         T up, down, ab;
         int p;
     };
+    static constexpr int kKept = 0;
+    static __device__ __forceinline__ void take(Node &, const T *, int) {}
+    static __device__ __forceinline__ void keep(const Node &, T *, int) {}
     static __device__ __forceinline__ void coefficients(const Env &e, Node &nd, T mii)
     {
         nd.c = e.L.xi + nd.kap + mii;
@@ -290,6 +312,10 @@ struct WgCycle {
     int levels, nu1, nu2, nuc;
     T *x;
     const T *rhs;
+    // first level whose nodes keep their power terms in LDS between visits (the
+    // launcher sets it by the LDS there is; never the top level, whose operator
+    // the cycle's fixed point depends on: it evaluates them afresh each visit)
+    int keep_from;
 };
 
 // Level memory as kernel arguments.
@@ -300,20 +326,41 @@ struct WgMems {
 };
 
 // LDS of the cycle: per level the iterate, K*, right-hand side, restricted
-// iterate (then the correction) and, FP32, the base state; one defect box of
-// the top level's size.
+// iterate (then the correction) and, FP32, the base state, or the kept power
+// terms; one defect box of the top level's size.
 template <typename T, int DIM>
-inline size_t wg_lds_bytes(const WgGeo &g, int levels)
+__host__ __device__ __forceinline__ int wg_words(const WgGeo &g, int s, int keep_from, int kept)
+{
+    return wg_level<DIM>(g, s).size * ((sizeof(T) == 4 ? 5 : 4) + (s >= keep_from ? kept : 0));
+}
+
+template <typename T, int DIM>
+inline size_t wg_lds_bytes(const WgGeo &g, int levels, int keep_from = kWgMaxLev, int kept = 0)
 {
     size_t w = 0;
-    for (int s = 0; s < levels; ++s)
-        w += (size_t)wg_level<DIM>(g, s).size * (sizeof(T) == 4 ? 5 : 4);
+    for (int s = 0; s < levels; ++s) w += (size_t)wg_words<T, DIM>(g, s, keep_from, kept);
     return sizeof(T) * (w + (size_t)wg_level<DIM>(g, 0).size);
+}
+
+// LDS for the cycle's boxes (of 160 KB, less a soil table).
+constexpr size_t kWgLds = 150 * 1024;
+
+// keep_from by the LDS there is; the bytes to launch with.
+template <typename T, int DIM>
+inline size_t wg_fit(WgCycle<T> *A, int kept)
+{
+    A->keep_from = kWgMaxLev;
+    for (int k = A->levels - 1; k >= 1 && kept > 0; --k) {
+        if (wg_lds_bytes<T, DIM>(A->g, A->levels, k, kept) > kWgLds) break;
+        A->keep_from = k;
+    }
+    return wg_lds_bytes<T, DIM>(A->g, A->levels, A->keep_from, kept);
 }
 
 template <typename T, int DIM>
 struct WgBox {
-    T *x, *K, *g, *bar, *pb;
+    T *x, *K, *g, *bar;
+    T *pb;   // FP32: base state; FP64: kept power terms
 };
 
 template <typename T, int DIM>
@@ -325,7 +372,7 @@ __device__ __forceinline__ WgBox<T, DIM> wg_box(T *lds, int off, const WgLevel<D
     b.K = q + v.size;
     b.g = q + 2 * v.size;
     b.bar = q + 3 * v.size;
-    b.pb = q + (sizeof(T) == 4 ? 4 : 0) * v.size;
+    b.pb = q + 4 * v.size;
     return b;
 }
 
@@ -363,7 +410,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
     const WgLevel<DIM> v = wg_level<DIM>(g, s);
     const WgBox<T, DIM> B = wg_box<T, DIM>(lds, off, v);
     const WgLevel<DIM> vc = wg_level<DIM>(g, s + 1);
-    const int noff = off + v.size * (sizeof(T) == 4 ? 5 : 4);
+    const int noff = off + wg_words<T, DIM>(g, s, A.keep_from, Op::kKept);
     const WgBox<T, DIM> C = wg_box<T, DIM>(lds, noff, vc);
     const bool last = s == A.levels - 1;
     const int tid = threadIdx.x;
@@ -398,6 +445,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                     q.soil = 0;
                     q.ps = pow_none();
                     if constexpr (Op::MODEL == kMulti) q.soil = M.soil[wg_mem<DIM>(g, v, c[col][u])];
+                    if (s >= A.keep_from) Op::take(q, B.pb, v.size);
                 } else {
                     q.base.psi = B.pb[q.p];
                 }
@@ -535,6 +583,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
             }
         }
     }
+    const bool keep = s >= A.keep_from;
     if (!up && !last && !norm_only) {
         // defect (0 at Dirichlet nodes), then its full weighting and the iterate's
         {
@@ -557,6 +606,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
 #pragma unroll
                     for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - xn[col][u][t]);
                     if (has[col][u]) dbox[q.p] = on[col][u] ? q.g - (loc + (lin1 + md)) : T(0);
+                    if (keep && has[col][u]) Op::keep(q, B.pb, v.size);
                 }
         }
         wg_sync<WAVE>();
@@ -614,7 +664,10 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
         for (int col = 0; col < 2; ++col)
 #pragma unroll
             for (int u = 0; u < S; ++u)
-                if (has[col][u]) B.bar[nd[col][u].p] = nd[col][u].x - B.bar[nd[col][u].p];
+                if (has[col][u]) {
+                    B.bar[nd[col][u].p] = nd[col][u].x - B.bar[nd[col][u].p];
+                    if (keep) Op::keep(nd[col][u], B.pb, v.size);
+                }
         wg_sync<WAVE>();
     } else if (norm) {
         double m = 0.0;
@@ -661,13 +714,12 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
 {
     typedef typename Op::T T;
     constexpr int DIM = Op::DIM;
-    constexpr int W = sizeof(T) == 4 ? 5 : 4;   // boxes per level
     const int nthreads = blockDim.x, tid = threadIdx.x;
     // every level's K* (and base state), the top level's iterate and
     // right-hand side; zeros elsewhere.  The loads of all levels that a pass of
     // the work-group covers are in flight together.
     int total = 0;
-    for (int s = 0; s < A.levels; ++s) total += W * wg_level<DIM>(A.g, s).size;
+    for (int s = 0; s < A.levels; ++s) total += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
     T *dbox = lds + total;
     const int all = total + wg_level<DIM>(A.g, 0).size;
     for (int t = tid; t < all; t += nthreads) lds[t] = T(0);
@@ -696,7 +748,7 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
                 B.K[wg_pos<DIM>(v, c)] = k0[s];
                 if (sizeof(T) == 4) B.pb[wg_pos<DIM>(v, c)] = p0[s];
             }
-            off += W * v.size;
+            off += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
         }
     off = 0;
     for (int s = 0; s < A.levels; ++s) {
@@ -718,7 +770,7 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
                 B.g[p] = A.rhs[at];
             }
         }
-        off += W * v.size;
+        off += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
     }
     __syncthreads();
     return dbox;
@@ -757,7 +809,6 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
 {
     typedef typename Op::T T;
     constexpr int DIM = Op::DIM;
-    constexpr int W = sizeof(T) == 4 ? 5 : 4;   // boxes per level
     T *dbox = wg_load<Op>(A, mem, lds);
     int off = 0;
     const int visits = 2 * A.levels - 1;
@@ -765,10 +816,10 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
     for (int q = 0; q < visits; ++q) {
         const bool up = q >= A.levels;
         const int s = up ? visits - 1 - q : q;
-        const int sz = wg_level<DIM>(A.g, s).size;
-        if (up) off -= W * sz;
+        const int words = wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+        if (up) off -= words;
         wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, nullptr, false);
-        if (!up && s + 1 < A.levels) off += W * sz;
+        if (!up && s + 1 < A.levels) off += words;
     }
 }
 
@@ -796,7 +847,6 @@ __device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const
 {
     typedef typename Op::T T;
     constexpr int DIM = Op::DIM;
-    constexpr int W = sizeof(T) == 4 ? 5 : 4;
     __shared__ double norm;
     T *dbox = wg_load<Op>(A, mem, lds);
     const int visits = 2 * A.levels - 1;
@@ -809,12 +859,12 @@ __device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const
     while (true) {
         const bool up = q >= A.levels;
         const int s = q < 0 ? 0 : (up ? visits - 1 - q : q);
-        const int sz = wg_level<DIM>(A.g, s).size;
-        if (up) off -= W * sz;
+        const int words = wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+        if (up) off -= words;
         const bool end = q < 0 || q == visits - 1;
         wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, end ? &norm : nullptr, q < 0);
         if (!end) {
-            if (!up && s + 1 < A.levels) off += W * sz;
+            if (!up && s + 1 < A.levels) off += words;
             ++q;
             continue;
         }

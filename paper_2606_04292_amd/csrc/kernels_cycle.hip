@@ -65,11 +65,12 @@ struct CycleWgLaunch {
     template <int MO, bool S, int D>
     void go()
     {
-        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
+        WgCycle<double> C = A;
+        const size_t bytes = wg_fit<double, D>(&C, WgOp64<MO, false, D>::kKept);
         if (bytes > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
+        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C, M,
                            law, a);
     }
 };
@@ -80,11 +81,12 @@ struct SolveWgLaunch {
     template <int MO, bool SK, int D>
     void go()
     {
-        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
+        WgCycle<double> C = A;
+        const size_t bytes = wg_fit<double, D>(&C, WgOp64<MO, false, D>::kKept);
         if (bytes > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)k_solve_wg<MO, SK, D>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_solve_wg<MO, SK, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
+        hipLaunchKernelGGL((k_solve_wg<MO, SK, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C,
                            M, law, a, S, out);
     }
 };
