@@ -1112,7 +1112,13 @@ __global__ __launch_bounds__(256) void k_defect_scale(Geo g, Law L, Step st, con
         }
     }
     v = block_max(v);
-    if (threadIdx.x == 0) atomicMax(out, (unsigned long long)__double_as_longlong(v));
+    if (threadIdx.x == 0) {
+        // only a group that raises the maximum makes the atomic: with one from each
+        // of the 33 000 groups of a 257x257x129 grid the launch took 391 us
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
+        if (bits > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(out, bits);
+    }
 }
 
 // ---------------------------------------------------------------------------
