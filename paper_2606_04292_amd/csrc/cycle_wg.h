@@ -316,6 +316,9 @@ struct WgCycle {
     // launcher sets it by the LDS there is; never the top level, whose operator
     // the cycle's fixed point depends on: it evaluates them afresh each visit)
     int keep_from;
+    // the coarsest level takes all its sweeps, also once no value moves (the
+    // sweeps of one level on their own, levels = 1)
+    int all;
 };
 
 // Level memory as kernel arguments.
@@ -577,8 +580,8 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
         if (last) {
             if (WAVE) {
                 wg_sync<true>();
-                if (!__any(changed)) break;
-            } else if (!__syncthreads_or(changed)) {
+                if (!A.all && !__any(changed)) break;
+            } else if (!__syncthreads_or(changed) && !A.all) {
                 break;
             }
         }
@@ -935,6 +938,8 @@ void launch_solve_wg(const WgCycle<double> &A, const WgMems<double> &M, const La
                      int dim, const WgSolve &S, WgSolveOut *out, hipStream_t s);
 void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
                      int dim, hipStream_t s);
+void launch_sweeps_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                      int dim, hipStream_t s);
 void launch_cycle_wg32(const WgCycle<float> &A, const WgMems<float> &M, const Law32 &law, float a,
                        int dim, hipStream_t s);
 

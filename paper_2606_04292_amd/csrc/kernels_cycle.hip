@@ -49,6 +49,29 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_solve_wg(WgCycle<double> A, W
     wg_solve<Op>(A, M, typename Op::Env{L, soils, a}, lds64, S, out);
 }
 
+// A.nuc sweeps of one level: the visit of the cycle's coarsest one, with no sweep
+// left out.  Bound by the chain of barriers and solves of one work-group, so the
+// level is loaded once and its nodes, face coefficients and power terms stay in
+// registers.  Against the kernel before it (global loads and a division per node
+// and sweep), two and twenty sweeps: 65 nodes 7.7 -> 6.0 and 55 -> 21 us, 513
+// nodes 15.2 -> 7.3 and 130 -> 32, 9^3 22.5 -> 9.4 and 203 -> 39 (vGM); against
+// one launch per colour 1025 nodes 18.6 -> 8.9 and 166 -> 40.
+template <int MODEL, bool SINK, int DIM>
+__global__ __launch_bounds__(kWgMaxThreads) void k_sweeps_wg(WgCycle<double> A, WgMems<double> M,
+                                                             Law L, double a)
+{
+    extern __shared__ double lds64[];
+    const Law *soils = stage_soils<MODEL>(L);
+    typedef WgOp64<MODEL, SINK, DIM> Op;
+    const typename Op::Env e{L, soils, a};
+    A.levels = 1;   // known here: the transfers drop out of the visit's code
+    A.keep_from = kWgMaxLev;
+    A.all = 1;
+    double *dbox = wg_load<Op>(A, M, lds64);
+    bool wave = false;
+    wg_visit_mode<Op>(A, M, e, 0, false, wave, lds64, 0, dbox, nullptr, false);
+}
+
 // One tile of a phase of a level (cycle_tile.h).
 template <int MODEL, bool SINK, int DIM>
 __global__ __launch_bounds__(kTileThreads) void k_cycle_tile(TileArgs<double> A, int phase, Law L,
@@ -72,6 +95,20 @@ struct CycleWgLaunch {
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C, M,
                            law, a);
+    }
+};
+
+struct SweepsWgLaunch {
+    const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; hipStream_t s;
+    template <int MO, bool S, int D>
+    void go()
+    {
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, 1);
+        if (bytes > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)k_sweeps_wg<MO, S, D>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        hipLaunchKernelGGL((k_sweeps_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
+                           M, law, a);
     }
 };
 
@@ -116,6 +153,12 @@ void launch_solve_wg(const WgCycle<double> &A, const WgMems<double> &M, const La
                      int dim, const WgSolve &S, WgSolveOut *out, hipStream_t s)
 {
     dispatch<true>(law, dim, SolveWgLaunch{A, M, law, a, S, out, s});
+}
+
+void launch_sweeps_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,
+                      int dim, hipStream_t s)
+{
+    dispatch<true>(law, dim, SweepsWgLaunch{A, M, law, a, s});
 }
 
 void launch_cycle_wg(const WgCycle<double> &A, const WgMems<double> &M, const Law &law, double a,

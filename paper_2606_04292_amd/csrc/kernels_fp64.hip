@@ -263,7 +263,7 @@ __device__ __forceinline__ double offrow_cf(const Geo &g, int o, int cl)
 // xl + 1 (a grid's levels have parity-split rows, see stencil_split; the
 // workspace arrays are padded, so both are always loaded, as one pair).
 template <int MODEL, bool SINK, int DIM>
-__device__ __forceinline__ bool ngs_cell_at(const Geo &g, const Law &L, double a,
+__device__ __forceinline__ void ngs_cell_at(const Geo &g, const Law &L, double a,
                                             const double *beta, double lambdaU, const double *K,
                                             const double *gv, double *psi, int i, int j, int k,
                                             long long idx, long long xl, int colour)
@@ -283,22 +283,8 @@ __device__ __forceinline__ bool ngs_cell_at(const Geo &g, const Law &L, double a
         Kn[q] = K[st.jn[q]];
         pn[q] = psi[st.jn[q]];
     }
-    const double x1 = ngs_point<MODEL, SINK, DIM>(g, L, a, beta, lambdaU, st, Ki, Kn, pn, f, x0, i,
-                                                  j, k, idx, colour);
-    psi[idx] = x1;
-    return fabs(x1 - x0) > 8.8817841970012523e-16 * fabs(x0);   // 4 ulp (2^-50 |x0|)
-}
-
-// The update of unknown (i, j, k); true if it moved the stored value by more
-// than 4 ulp.
-template <int MODEL, bool SINK, int DIM>
-__device__ __forceinline__ bool ngs_cell(const Geo &g, const Law &L, double a, const double *beta,
-                                         double lambdaU, const double *K, const double *gv,
-                                         double *psi, int i, int j, int k, int colour)
-{
-    const long long idx = lin(g, i, j, k);
-    return ngs_cell_at<MODEL, SINK, DIM>(g, L, a, beta, lambdaU, K, gv, psi, i, j, k, idx,
-                                         xnb(g, i, idx, -1), colour);
+    psi[idx] = ngs_point<MODEL, SINK, DIM>(g, L, a, beta, lambdaU, st, Ki, Kn, pn, f, x0, i, j, k,
+                                           idx, colour);
 }
 
 // ---------------------------------------------------------------------------
@@ -947,30 +933,6 @@ __global__ __launch_bounds__(256) void k_sweep_zm(Geo g, Law L, Step st, const d
     }
 }
 
-// Whole sweeps of a tiny level in one work-group (the coarsest levels, where
-// launch latency, not work, dominates).
-template <int MODEL, bool SINK, int DIM>
-__global__ __launch_bounds__(256) void k_sweep_small(Geo g, Law L, Step st, const double *beta,
-                                                     double lambdaU, const double *K,
-                                                     const double *gv, double *psi, int nsweeps)
-{
-    const int N = (int)g.N;
-    for (int s = 0; s < nsweeps; ++s) {
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int t = threadIdx.x; t < N; t += blockDim.x) {
-                int i = t % g.n[0];
-                int r = t / g.n[0];
-                int j = r % g.n[1];
-                int k = r / g.n[1];
-                if (((i + j + k) & 1) != colour) continue;
-                if (dirichlet_t<DIM>(g, i, j, k)) continue;
-                ngs_cell<MODEL, SINK, DIM>(g, L, st.a, beta, lambdaU, K, gv, psi, i, j, k, colour);
-            }
-            __syncthreads();
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Defect d = g - N(psi) and its max-norm (step 2 of the FAS algorithm)
 // ---------------------------------------------------------------------------
@@ -1360,11 +1322,6 @@ struct SweepLaunch {
     template <int M, bool S, int D>
     void go()
     {
-        if (g.N <= 1024) {
-            hipLaunchKernelGGL((k_sweep_small<M, S, D>), dim3(1), dim3(256), 0, s, g, law, st,
-                               beta, lambdaU, K, gvec, *psi, nsweeps);
-            return;
-        }
         if (D == 3 && psi_alt && *psi_alt && fused_enabled()) {
             FusedMap fm = fused_map(g);
             const size_t lds = sizeof(double) * 4 * (size_t)fm.LX * fm.LY;
@@ -1500,7 +1457,6 @@ int launch_sweep_rb(const Geo &g, const Law &law, const Step &st, const double *
 {
     if (nsweeps <= 0) return 0;
     dispatch<true>(law, g.dim, SweepLaunch{g, law, st, beta, lambdaU, K, gvec, psi, psi_alt, nsweeps, s});
-    if (g.N <= 1024) return 1;
     return (g.dim == 3 && psi_alt && *psi_alt && fused_enabled()) ? nsweeps : 2 * nsweeps;
 }
 

@@ -13,6 +13,7 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2606_04292_amd as rsl
@@ -76,6 +77,29 @@ def test_vcycles_match_the_oracle(name):
         e = rel(np_(G.psi()), S.psi())
         say("  cycle", c, "rel", e)
         assert e <= TOL_SWEEP, (name, c, e)
+    G.close()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_sweeps_of_one_level_match_the_oracle(name):
+    """Sweeps on their own (one launch in one work-group where the level fits
+    it), an odd number and a second batch, on the finest and coarsest level."""
+    w = CASES[name]
+    say("wg sweeps", name, w.grid.n)
+    S = oracle.Solver(w, oracle.ORDER_RB)
+    G = rsl.Grid(w)
+    S.begin_step()
+    G.begin_step()
+    for lev in sorted({0, S.nlev - 1}):
+        for f in ("PSI", "KSTAR", "G"):
+            G.set_field(getattr(rsl, "FIELD_" + f),
+                        torch.as_tensor(S.get(getattr(oracle, "FIELD_" + f), lev)), lev)
+        for n in (3, 2):
+            S.sweep(n, lev)
+            G.sweep(n, lev)
+            e = rel(np_(G.psi(lev)), S.psi(lev))
+            say("  level", lev, "sweeps", n, "rel", e)
+            assert e <= TOL_SWEEP, (name, lev, n, e)
     G.close()
 
 
