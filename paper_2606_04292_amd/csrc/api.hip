@@ -326,7 +326,7 @@ Law make_law(const rs_constitutive *c)
     switch (c->model) {
     case RS_HAVERKAMP:
         L.c_th = L.hk_alpha * L.dT;
-        L.c_dth = L.unit * L.hk_beta * L.c_th;
+        L.c_dth = L.unit * L.hk_beta;
         break;
     case RS_VGM:
         L.c_th = L.dT;

@@ -129,7 +129,7 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
             q.b = Op::SINK ? (T)A.beta[cc[DIM - 1]] : T(0);
             if constexpr (sizeof(T) == 8) {
                 q.soil = 0;
-                q.ps = pow_none();
+                q.ps = kept_none();
                 if constexpr (Op::MODEL == kMulti) q.soil = A.soil[at];
             } else {
                 q.base.psi = A.pb[at];
@@ -169,10 +169,12 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
             for (int l = 0; l < DIM; ++l) {
                 const bool lo = cc[l] == 0, hi = cc[l] == v.n[l] - 1;
                 const double cf = (lo || hi ? 1.0 : 0.5) * g.ih2[l];
-                q.m[2 * l] = lo ? T(0) : (T)cf * (Kc[col] + Kn[col][2 * l]);
-                q.m[2 * l + 1] = hi ? T(0) : (T)cf * (Kc[col] + Kn[col][2 * l + 1]);
-                mii += q.m[2 * l];
-                mii += q.m[2 * l + 1];
+                const T cl = lo ? T(0) : (T)cf, ch = hi ? T(0) : (T)cf;
+                const T kl = Kc[col] + Kn[col][2 * l], kh = Kc[col] + Kn[col][2 * l + 1];
+                q.m[2 * l] = cl * kl;
+                q.m[2 * l + 1] = ch * kh;
+                mii = fma(cl, kl, mii);   // as the launched kernels' sum contracts
+                mii = fma(ch, kh, mii);
             }
             if (e.L.kappa_rule == kKappaConst) q.kap = (T)e.L.kappa;
             else if (e.L.kappa_rule == kKappaRel) q.kap = (T)e.L.kappa * mii;
@@ -257,7 +259,7 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
         qc.b = Op::SINK ? (T)A.betac[ccl[DIM - 1]] : T(0);
         if constexpr (sizeof(T) == 8) {
             qc.soil = 0;
-            qc.ps = pow_none();
+            qc.ps = kept_none();
             if constexpr (Op::MODEL == kMulti) qc.soil = A.soilc[atc];
         } else {
             qc.base = base_of<Op::MODEL>(e.L, A.pbc[atc]);

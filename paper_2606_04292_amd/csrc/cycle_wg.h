@@ -190,7 +190,7 @@ struct WgOp64 {
     };
     struct Node {
         T m[2 * DIM], c, ic, kap, x, g, b;
-        PowState ps;   // power terms of the last evaluation of this visit
+        PowKept ps;   // power terms of the last evaluation of this visit
         int p, soil;
     };
     // Values per node that carry the power terms from one visit to the next: for
@@ -234,9 +234,9 @@ struct WgOp64 {
     {
         if constexpr (MODEL == kMulti) {
             const Law &Ls = e.soils[nd.soil];
-            return local_solve_soil_ic<SINK, 0>(Ls, e.a, nd.b, nd.c, nd.ic, f, nd.x, nd.ps);
+            return local_solve_soil_ic<SINK, 0, true>(Ls, e.a, nd.b, nd.c, nd.ic, f, nd.x, nd.ps);
         } else {
-            return local_solve_ic<MODEL, SINK, 0, false, true>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x,
+            return local_solve_ic<MODEL, SINK, 0, true, true>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x,
                                                                nd.ps);
         }
     }
@@ -446,7 +446,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                 q.b = Op::SINK ? (T)M.beta[c[col][u][DIM - 1]] : T(0);
                 if constexpr (sizeof(T) == 8) {
                     q.soil = 0;
-                    q.ps = pow_none();
+                    q.ps = kept_none();
                     if constexpr (Op::MODEL == kMulti) q.soil = M.soil[wg_mem<DIM>(g, v, c[col][u])];
                     if (s >= A.keep_from) Op::take(q, B.pb, v.size);
                 } else {
@@ -467,10 +467,12 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                 for (int l = 0; l < DIM; ++l) {
                     const bool lo = cc[l] == 0, hi = cc[l] == v.n[l] - 1;
                     const double cf = (lo || hi ? 1.0 : 0.5) * ih[l];
-                    q.m[2 * l] = lo ? T(0) : (T)cf * (Kc[col][u] + Kn[col][u][2 * l]);
-                    q.m[2 * l + 1] = hi ? T(0) : (T)cf * (Kc[col][u] + Kn[col][u][2 * l + 1]);
-                    mii += q.m[2 * l];
-                    mii += q.m[2 * l + 1];
+                    const T cl = lo ? T(0) : (T)cf, ch = hi ? T(0) : (T)cf;
+                    const T kl = Kc[col][u] + Kn[col][u][2 * l], kh = Kc[col][u] + Kn[col][u][2 * l + 1];
+                    q.m[2 * l] = cl * kl;
+                    q.m[2 * l + 1] = ch * kh;
+                    mii = fma(cl, kl, mii);   // as the launched kernels' sum contracts
+                    mii = fma(ch, kh, mii);
                 }
                 if (e.L.kappa_rule == kKappaConst) q.kap = (T)e.L.kappa;
                 else if (e.L.kappa_rule == kKappaRel) q.kap = (T)e.L.kappa * mii;

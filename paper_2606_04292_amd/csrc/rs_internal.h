@@ -64,7 +64,7 @@ struct Law {
     double newton_tol;   // a Newton step of at most newton_tol |x| ends the pointwise solve
     double gd_alpha;     // Gardner exponent (per law unit of psi)
     const Law *soils;    // kMulti: device table of per-soil laws, indexed by Geo::soil
-    // theta - theta_r = c_th s and theta' = c_dth ds of law_unsat (soil_device.h)
+    // uniform factors of theta - theta_r and theta' (theta_next, soil_device.h)
     double c_th, c_dth;
     // binomial coefficients binom(e, k), k = 1..7, of (1 + u)^e - 1: e = hk_beta
     // (Haverkamp) or vg_n (vGM) in bin1, e = -vg_m (vGM) in bin2; the series is

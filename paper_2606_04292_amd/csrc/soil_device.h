@@ -41,23 +41,11 @@ __device__ __forceinline__ double rcp_1nr(double x)
 
 // Natural logarithm of a positive normal double.  x = m 2^e with m in
 // [sqrt(1/2), sqrt(2)), ln x = e ln2 + 2 atanh(s), s = (m-1)/(m+1), |s| <= 0.1716,
+// with the atanh series 2 s (1 + s^2/3 + ... + s^18/19) (truncation < 3e-17)
 // and ln2 split Cody-Waite style so that e ln2_hi is exact.
 constexpr double kLn2Hi = 6.93147180369123816490e-01;
 constexpr double kLn2Lo = 1.90821492927058770002e-10;
 constexpr double kInvLn2 = 1.44269504088896338700e+00;
-
-// A value that every lane of the wave holds, in a scalar register pair (there is
-// no scalar FP64 arithmetic: a product of kernel arguments lands in vector
-// registers, two per value, for as long as it lives).
-template <bool PER_LANE>
-__device__ __forceinline__ double uniform_f64(double v)
-{
-    if (PER_LANE) return v;
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 // p * r + c with the coefficient c in a scalar register pair (one VOP3 FMA;
 // no vector moves to materialise the constant).
@@ -68,22 +56,19 @@ __device__ __forceinline__ double fma_sc(double p, double r, double c)
     return out;
 }
 
-// 2 atanh(s) = 2 s + 2 s^3 R(s^2), R the degree-7 polynomial of least relative
-// error over |s| <= 0.1716 (Remez exchange: 8.2e-21).  Against 50-digit values at
-// 40000 points 0.500 ulp at most and 0.183 on average, as the nine-term Taylor
-// series it replaces (0.500, 0.184).
 __device__ __forceinline__ double atanh2_series(double s)
 {
     const double s2 = s * s;
-    double p = 0.06625447453546243;
-    p = fma_sc(p, s2, 0.0662508549448883);
-    p = fma_sc(p, s2, 0.07693544063083087);
-    p = fma_sc(p, s2, 0.0909088786714923);
-    p = fma_sc(p, s2, 0.11111111322895023);
-    p = fma_sc(p, s2, 0.1428571428454699);
-    p = fma_sc(p, s2, 0.20000000000003107);
-    p = fma_sc(p, s2, 0.3333333333333333);
-    return fma(2.0 * s * s2, p, 2.0 * s);
+    double p = 1.0 / 19.0;
+    p = fma_sc(p, s2, 1.0 / 17.0);
+    p = fma_sc(p, s2, 1.0 / 15.0);
+    p = fma_sc(p, s2, 1.0 / 13.0);
+    p = fma_sc(p, s2, 1.0 / 11.0);
+    p = fma_sc(p, s2, 1.0 / 9.0);
+    p = fma_sc(p, s2, 1.0 / 7.0);
+    p = fma_sc(p, s2, 1.0 / 5.0);
+    p = fma_sc(p, s2, 1.0 / 3.0);
+    return fma(2.0 * s * s2, p, 2.0 * s);   // 2 atanh(s)
 }
 
 __device__ __forceinline__ double rs_log(double x)
@@ -107,26 +92,26 @@ __device__ __forceinline__ double rs_log1p(double p)
     return rs_log(1.0 + p);
 }
 
-// e^y: y = n ln2 + r (Cody-Waite, |r| <= ln2/2), e^r = 1 + r + r^2/2 + r^3 q(r)
-// with q the degree-9 polynomial of least error (Remez exchange: 5.4e-20 in e^r),
-// scaled by 2^n (overflows to inf, underflows to 0 past the double range).
-// Against 50-digit values at 40000 points 0.605 ulp at most and 0.186 on
-// average, as the Taylor series to r^13/13! it replaces.
+// e^y: y = n ln2 + r (Cody-Waite, |r| <= ln2/2), e^r by its Taylor series to
+// r^13/13! (truncation < 5e-18), scaled by 2^n (overflows to inf, underflows
+// to 0 past the double range).
 __device__ __forceinline__ double rs_exp(double y)
 {
-    const double n = rint(y * kInvLn2);
+    double n = rint(y * kInvLn2);
+    n = fmin(fmax(n, -2100.0), 2100.0);
     double r = fma(-n, kLn2Hi, y);
     r = fma(-n, kLn2Lo, r);
-    double p = 2.0925702139195154e-09;
-    p = fma_sc(p, r, 2.5112179532238123e-08);
-    p = fma_sc(p, r, 2.755723860719594e-07);
-    p = fma_sc(p, r, 2.755723443702197e-06);
-    p = fma_sc(p, r, 2.48015873651743e-05);
-    p = fma_sc(p, r, 0.00019841269896820335);
-    p = fma_sc(p, r, 0.0013888888888865139);
-    p = fma_sc(p, r, 0.008333333333316859);
-    p = fma_sc(p, r, 0.0416666666666667);
-    p = fma_sc(p, r, 0.16666666666666682);
+    double p = 1.0 / 6227020800.0;                   // 1/13!
+    p = fma_sc(p, r, 1.0 / 479001600.0);
+    p = fma_sc(p, r, 1.0 / 39916800.0);
+    p = fma_sc(p, r, 1.0 / 3628800.0);
+    p = fma_sc(p, r, 1.0 / 362880.0);
+    p = fma_sc(p, r, 1.0 / 40320.0);
+    p = fma_sc(p, r, 1.0 / 5040.0);
+    p = fma_sc(p, r, 1.0 / 720.0);
+    p = fma_sc(p, r, 1.0 / 120.0);
+    p = fma_sc(p, r, 1.0 / 24.0);
+    p = fma_sc(p, r, 1.0 / 6.0);
     p = fma(p, r, 0.5);
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
@@ -148,8 +133,97 @@ __device__ __forceinline__ double pow1p_m1_series(double u, const double *c)
     return p * u;
 }
 
-// Power terms of the last law evaluation at a node.
+// Power terms of a law evaluation.
 struct PowState {
+    bool ok;       // there is one, of an unsaturated value (Haverkamp, vGM)
+    double x;      // that value
+    double ix;     // 1 / x
+    double q;      // Haverkamp: Q = (unit |x|)^beta; vGM: P = (alpha |x|)^n
+    double se;     // vGM: Se = (1 + P)^-m
+    double ix1p;   // vGM: 1 / (1 + P)
+};
+
+__device__ __forceinline__ PowState pow_none()
+{
+    return PowState{false, 0.0, 0.0, 0.0, 1.0, 0.0};
+}
+
+struct ThetaEval {
+    double th;
+    double dth;
+};
+
+// theta and theta' at x within one pointwise solve.  The power terms of the
+// Haverkamp and vGM laws scale from the last iterate's: Q(x) = Q(x') (1 + u)^beta
+// and P(x) = P(x') (1 + u)^n with u = x / x' - 1, then Se(x) = Se(x') (1 + v)^-m
+// with v = (P(x) - P(x')) / (1 + P(x')); each factor is taken by the binomial
+// series while its u or v is below L.series_u (2^-8; 0 for exponents outside
+// [-1, 7]) in magnitude, else the powers are evaluated afresh.
+template <int MODEL>
+__device__ __forceinline__ ThetaEval theta_next(const Law &L, double x, PowState &s)
+{
+    ThetaEval r;
+    if (MODEL == kLinear) {
+        r.th = L.tr + L.lin_c * x;
+        r.dth = L.lin_c;
+        return r;
+    }
+    if (!(x < 0.0)) {
+        r.th = L.ts;
+        r.dth = 0.0;
+        s.ok = false;
+        return r;
+    }
+    if (MODEL == kGardner) {
+        const double E = rs_exp(L.gd_alpha * L.unit * x);
+        r.th = L.tr + L.c_th * E;
+        r.dth = L.c_dth * E;
+        return r;
+    }
+    const double u = (x - s.x) * s.ix;
+    const bool ser = s.ok && fabs(u) < L.series_u;
+    if (MODEL == kHaverkamp) {
+        const double hu = -L.unit * x;
+        double Q;
+        if (ser) Q = fma(s.q, pow1p_m1_series(u, L.bin1), s.q);
+        else Q = rs_exp(L.hk_beta * rs_log(hu));
+        // one reciprocal serves 1/(alpha + Q) = hu w and 1/hu = (alpha + Q) w
+        const double den = L.hk_alpha + Q;
+        const double w = rcp_1nr(hu * den);
+        const double tmr = L.c_th * (hu * w);      // theta - theta_r
+        r.th = L.tr + tmr;
+        r.dth = L.c_dth * tmr * Q * w;
+        s.q = Q;
+        s.ix = -L.unit * (den * w);   // 1/x = -unit / hu
+    } else {
+        double P = 0.0, Se = 0.0;
+        bool fresh = !ser;
+        if (ser) {
+            const double dP = s.q * pow1p_m1_series(u, L.bin1);
+            const double v = dP * s.ix1p;
+            P = s.q + dP;
+            if (fabs(v) < L.series_u) Se = fma(s.se, pow1p_m1_series(v, L.bin2), s.se);
+            else fresh = true;
+        }
+        if (fresh) {
+            P = rs_exp(L.vg_n * rs_log(-L.vg_alpha * x));
+            Se = rs_exp(-L.vg_m * rs_log1p(P));
+        }
+        const double w = rcp_1nr((1.0 + P) * (-x));
+        r.th = L.tr + L.c_th * Se;
+        r.dth = L.c_dth * P * Se * w;
+        s.q = P;
+        s.se = Se;
+        s.ix = -(1.0 + P) * w;
+        s.ix1p = -x * w;
+    }
+    s.x = x;
+    s.ok = true;
+    return r;
+}
+
+// Power terms of the last law evaluation at a node.
+struct PowKept {
     bool ok;       // the last iterate was unsaturated (Haverkamp, vGM)
     double h;      // its magnitude: unit |x| (Haverkamp), |x| (vGM)
     double ih;     // 1 / h
@@ -160,19 +234,19 @@ struct PowState {
 
 // The state behind a magnitude and the vGM power terms that were kept (h = 0:
 // none).
-__device__ __forceinline__ PowState pow_kept(double h, double q, double se)
+__device__ __forceinline__ PowKept pow_kept(double h, double q, double se)
 {
     const double X = 1.0 + q, w = rcp_1nr(X * h);
-    return PowState{h > 0.0, h, X * w, q, se, h * w};
+    return PowKept{h > 0.0, h, X * w, q, se, h * w};
 }
 
-__device__ __forceinline__ PowState pow_none()
+__device__ __forceinline__ PowKept kept_none()
 {
-    return PowState{false, 0.0, 0.0, 0.0, 1.0, 0.0};
+    return PowKept{false, 0.0, 0.0, 0.0, 1.0, 0.0};
 }
 
 // The law at x < 0 within the visits of one node: theta - theta_r = L.c_th s and
-// theta' = L.c_dth ds.  The power terms of the Haverkamp and vGM laws scale from
+// theta' = law_slope(L) ds.  The power terms of the Haverkamp and vGM laws scale from
 // the last iterate's: Q(x) = Q(x') (1 + u)^beta and P(x) = P(x') (1 + u)^n with
 // u = x / x' - 1, then Se(x) = Se(x') (1 + v)^-m with v = (P(x) - P(x')) / (1 + P(x'));
 // each factor is taken by the binomial series while its u or v is below
@@ -182,7 +256,7 @@ __device__ __forceinline__ PowState pow_none()
 // times the exponent of a fresh evaluation.  NR2: two Newton-Raphson steps in
 // the reciprocal that enters theta, for values that enter a defect.
 template <int MODEL, bool NR2 = false>
-__device__ __forceinline__ void law_unsat(const Law &L, double x, PowState &p, double &s,
+__device__ __forceinline__ void law_unsat(const Law &L, double x, PowKept &p, double &s,
                                           double &ds)
 {
     if (MODEL == kLinear) {
@@ -234,6 +308,12 @@ __device__ __forceinline__ void law_unsat(const Law &L, double x, PowState &p, d
         p.ix1p = h * w;
         p.ok = true;
     }
+}
+
+template <int MODEL>
+__device__ __forceinline__ double law_slope(const Law &L)
+{
+    return MODEL == kHaverkamp ? L.c_dth * L.c_th : L.c_dth;
 }
 
 template <int MODEL>
@@ -293,7 +373,7 @@ __device__ __forceinline__ void feddes(const Law &L, double x, double &a, double
 // law_unsat where every active lane of the wave is unsaturated and within the
 // series' range of its last evaluation; false (and nothing done) otherwise.
 template <int MODEL>
-__device__ __forceinline__ bool law_scaled(const Law &L, double x, PowState &p, double &s,
+__device__ __forceinline__ bool law_scaled(const Law &L, double x, PowKept &p, double &s,
                                            double &ds)
 {
     const double h = MODEL == kHaverkamp ? -L.unit * x : -x;
@@ -334,63 +414,58 @@ __device__ __forceinline__ bool law_scaled(const Law &L, double x, PowState &p, 
 // the step leaves the iterate unchanged.  A Newton step (not a bisection) that
 // moves x by at most L.newton_tol |x_new| ends the solve for that cell: the
 // steps left out would move it by about that step squared times F''/2F'.
-// ic = rcp_nr(c) (unused by the linear law); ps: the power terms of the node's
-// last evaluation (pow_none() if there is none), left at those of the solve's
-// last one.  A wave issues one instruction every 6 to 7 cycles whatever its
-// kind, so the loop is written for few of them: F as v + (c x - (f - a theta_r))
-// with v = a (theta - theta_r), uniform factors of the law formed once, selects
-// instead of branches, the bisection only where some lane needs it.
-// PER_LANE: the law differs between lanes (layered media).  KEPT: ps usually
-// holds the node's last evaluation.
-template <int MODEL, bool SINK, int NEWTON, bool PER_LANE = false, bool KEPT = false>
+// ic = rcp_nr(c) (unused by the linear law).  A wave issues one instruction every
+// 6 to 7 cycles whatever its kind, so the loop has selects instead of branches and
+// the bisection only where some lane needs it.  F is formed as the defect forms its
+// terms, a (theta_r + ...): a product of a and the law's scale rounded once for the
+// whole grid (one instruction less) moved the fixed point of every node one way,
+// by up to 2 half-ulps of psi.
+// KEPT: pk holds the node's last evaluation (WAVE: scaled without a branch per lane
+// where the whole wave is close to it).
+template <int MODEL, bool SINK, int NEWTON, bool KEPT = false, bool WAVE = false>
 __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double beta, double c,
-                                                 double ic, double f, double x0, PowState &ps)
+                                                 double ic, double f, double x0, PowKept &pk)
 {
-    const double ath = uniform_f64<PER_LANE>(a * L.c_th), adth = uniform_f64<PER_LANE>(a * L.c_dth);
-    const double as = uniform_f64<PER_LANE>(a * L.dT);
-    const double fr = f - a * L.tr;
     double lo, hi;
     if (MODEL == kLinear) {
         lo = -INFINITY;
         hi = INFINITY;
     } else {
         lo = (f - a * L.ts - beta) * ic;
-        hi = fr * ic;
+        hi = (f - a * L.tr) * ic;
         const double pad = 1e-12 * (fabs(lo) + fabs(hi));
         lo -= pad;
         hi += pad;
     }
     double x = x0;
     bool done = false;
+    PowState ps = pow_none();
     // three copies of the iteration pay for the Haverkamp law (257^3 sweep 89.8 ->
     // 88.1 us); of the longer vGM law with a sink they spill scalar registers
     // (root box, a step: 13.3 -> 14.1 ms)
     const int iters = NEWTON > 0 ? NEWTON : L.newton;
 #pragma clang loop unroll_count(NEWTON == 3 && MODEL == kHaverkamp ? 3 : 1)
     for (int k = 0; k < iters; ++k) {
-        double v = 0.0, dF = 0.0, s, ds;
-        bool scaled = false;
-        if constexpr (KEPT && (MODEL == kHaverkamp || MODEL == kVgm)) {
-            // the whole wave unsaturated and close to its last evaluations: the
-            // powers scale without a branch per lane
-            if (law_scaled<MODEL>(L, x, ps, s, ds)) {
-                v = ath * s;
-                dF = fma(adth, ds, c);
-                scaled = true;
-            }
-        }
-        if (!scaled) {
-            v = as;   // saturated: theta_s, theta' = 0
-            dF = c;
-            if (MODEL == kLinear || x < 0.0) {
-                law_unsat<MODEL>(L, x, ps, s, ds);
-                v = ath * s;
-                dF = fma(adth, ds, c);
+        ThetaEval t;
+        if constexpr (KEPT) {
+            double s = 0.0, ds = 0.0;
+            bool near = false;
+            if constexpr (WAVE && (MODEL == kHaverkamp || MODEL == kVgm))
+                near = law_scaled<MODEL>(L, x, pk, s, ds);
+            t.th = L.ts;   // saturated
+            t.dth = 0.0;
+            if (near || MODEL == kLinear || x < 0.0) {
+                if (!near) law_unsat<MODEL>(L, x, pk, s, ds);
+                t.th = L.tr + L.c_th * s;
+                t.dth = law_slope<MODEL>(L) * ds;
             } else {
-                ps.ok = false;
+                pk.ok = false;
             }
+        } else {
+            t = theta_next<MODEL>(L, x, ps);
         }
-        double F = v + fma(c, x, -fr);
+        double F = fma(c, x, a * t.th) - f;
+        double dF = fma(a, t.dth, c);
         if (SINK) {
             double fa, dfa;
             feddes(L, x, fa, dfa);
@@ -401,7 +476,7 @@ __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double 
         const bool pos = F > 0.0, neg = F < 0.0;
         hi = (pos & !(hi <= x)) ? x : hi;
         lo = (neg & !(lo >= x)) ? x : lo;
-        double xn = fma(-F, rcp_1nr(dF), x);
+        double xn = x - F * rcp_1nr(dF);
         const bool bisect = !(dF > 0.0) | ((xn != x) & !((xn > lo) & (xn < hi)));
         // (at a root, or where F is not a number, the value stays)
         if (__builtin_amdgcn_ballot_w64(bisect) != 0 && bisect) xn = (pos | neg) ? 0.5 * (lo + hi) : x;
@@ -419,23 +494,23 @@ template <int MODEL, bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_t(const Law &L, double a, double beta, double c,
                                                 double f, double x0)
 {
-    PowState ps = pow_none();
-    return local_solve_ic<MODEL, SINK, NEWTON>(L, a, beta, c,
-                                               MODEL == kLinear ? 0.0 : rcp_nr(c), f, x0, ps);
+    PowKept pk = kept_none();
+    return local_solve_ic<MODEL, SINK, NEWTON>(L, a, beta, c, MODEL == kLinear ? 0.0 : rcp_nr(c),
+                                               f, x0, pk);
 }
 
 // The pointwise solve with the law of one soil picked at run time (layered
 // media): the same iteration as local_solve_t for that soil's model.
-template <bool SINK, int NEWTON>
+template <bool SINK, int NEWTON, bool KEPT = false>
 __device__ __forceinline__ double local_solve_soil_ic(const Law &Ls, double a, double beta,
                                                       double c, double ic, double f, double x0,
-                                                      PowState &ps)
+                                                      PowKept &pk)
 {
     switch (Ls.model) {
-    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
-    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
-    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
-    default: return local_solve_ic<kLinear, SINK, NEWTON, true>(Ls, a, beta, c, ic, f, x0, ps);
+    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
+    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
+    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
+    default: return local_solve_ic<kLinear, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
     }
 }
 
@@ -443,13 +518,13 @@ template <bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_soil(const Law &Ls, double a, double beta, double c,
                                                    double f, double x0)
 {
-    PowState ps = pow_none();
-    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0, ps);
+    PowKept pk = kept_none();
+    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0, pk);
 }
 
 // theta at x for a defect, from the power terms of the node's last evaluation.
 template <int MODEL>
-__device__ __forceinline__ double theta_defect(const Law &L, double x, PowState &ps)
+__device__ __forceinline__ double theta_defect(const Law &L, double x, PowKept &ps)
 {
     if constexpr (MODEL == kMulti) {
         switch (L.model) {
