@@ -468,8 +468,8 @@ hipError_t prof_slot(rs_grid *G)
 
 // Levels whose sweeps run in one work-group, all in one launch (k_sweeps_wg):
 // what fits it.  One sweep of a 2049-node column, two nodes per thread and
-// colour, takes 10.7 us there against 9.1 in two launches, two sweeps 13.2
-// against 18.4: such a level takes it from two sweeps on.  RS_SWEEP set keeps
+// colour, takes 10.7 us there against 9.1 in two launches, two sweeps 15.1
+// against 19.4: such a level takes it from two sweeps on.  RS_SWEEP set keeps
 // levels of more than 1024 nodes with the sweep kernels.
 bool wg_sweep_level(const LevelData &f, int nsweeps)
 {

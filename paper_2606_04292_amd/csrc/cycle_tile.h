@@ -129,7 +129,6 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
             q.b = Op::SINK ? (T)A.beta[cc[DIM - 1]] : T(0);
             if constexpr (sizeof(T) == 8) {
                 q.soil = 0;
-                q.ps = kept_none();
                 if constexpr (Op::MODEL == kMulti) q.soil = A.soil[at];
             } else {
                 q.base.psi = A.pb[at];
@@ -259,7 +258,6 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
         qc.b = Op::SINK ? (T)A.betac[ccl[DIM - 1]] : T(0);
         if constexpr (sizeof(T) == 8) {
             qc.soil = 0;
-            qc.ps = kept_none();
             if constexpr (Op::MODEL == kMulti) qc.soil = A.soilc[atc];
         } else {
             qc.base = base_of<Op::MODEL>(e.L, A.pbc[atc]);
@@ -270,12 +268,10 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
 #pragma unroll
     for (int col = 0; col < 2; ++col) {
         typename Op::Node &q = nd[col];
-        T lin1;
-        const T loc = Op::local(e, q, q.x, lin1);
         T md = T(0);
 #pragma unroll
         for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - lx[q.p + so[t]]);
-        const T r = on[col] ? q.g - (loc + (lin1 + md)) : T(0);
+        const T r = on[col] ? q.g - Op::template apply<true>(e, q, q.x, md) : T(0);
         if (has[col]) lk[q.p] = r;
         if (mine[col]) {
             const double ar = fabs((double)r);
@@ -346,9 +342,7 @@ __device__ __forceinline__ void tile_run(const TileArgs<typename Op::T> &A, int 
                 md += ml * (xb - (lo ? xb : lc[p - st]));
                 md += mh * (xb - (hi ? xb : lc[p + st]));
             }
-            T lin1;
-            const T loc = Op::local(e, qc, xb, lin1);
-            gc = (loc + (lin1 + md)) + gc;
+            gc = Op::template apply<true>(e, qc, xb, md) + gc;
         }
         A.bar[atc] = xb;
         A.rhsc[atc] = gc;

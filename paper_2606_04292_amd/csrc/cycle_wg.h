@@ -10,9 +10,10 @@
 //    and a missing one reads any finite value under a zero coefficient;
 //  - a thread owns the same red and black nodes for a whole visit of a level
 //    and keeps their face coefficients, diagonal and its reciprocal,
-//    right-hand side, own value and (FP64) the power terms of its last law
-//    evaluation in registers: a colour pass reads 2 DIM neighbour values,
-//    solves (the powers scaled from the last evaluation's) and writes one value;
+//    right-hand side and own value in registers: a colour pass reads 2 DIM
+//    neighbour values, solves and writes one value.  Power terms of the law are
+//    not carried from solve to solve: scaled on from one to the next, their
+//    roundings add up (5.8 half-ulps of psi rms after ten visits against 2.8);
 //  - nodes of one colour are the even (odd) positions of the lexicographic
 //    order (all axes have an odd node count), so slots map to nodes without
 //    padding; levels of at most 64 nodes per colour run on one wave without
@@ -190,54 +191,39 @@ struct WgOp64 {
     };
     struct Node {
         T m[2 * DIM], c, ic, kap, x, g, b;
-        PowKept ps;   // power terms of the last evaluation of this visit
         int p, soil;
     };
-    // Values per node that carry the power terms from one visit to the next: for
-    // the vGM law, whose fresh evaluation is two logarithms and two exponentials
-    // (a 257-node column's step 1.93 -> 1.81 ms; with the Haverkamp law or
-    // per-node soils the cycle got slower by 5 %)
-    static constexpr int kKept = MODEL == kVgm ? 3 : 0;
-    static __device__ __forceinline__ void take(Node &nd, const T *kept, int stride)
-    {
-        if constexpr (kKept > 0)
-            nd.ps = pow_kept(kept[nd.p], kept[stride + nd.p], kept[2 * stride + nd.p]);
-    }
-    static __device__ __forceinline__ void keep(const Node &nd, T *kept, int stride)
-    {
-        if constexpr (kKept > 0) {
-            kept[nd.p] = nd.ps.ok ? nd.ps.h : 0.0;
-            kept[stride + nd.p] = nd.ps.q;
-            kept[2 * stride + nd.p] = nd.ps.se;
-        }
-    }
     static __device__ __forceinline__ void coefficients(const Env &e, Node &nd, T mii)
     {
         nd.c = e.L.xi + nd.kap + mii;
         nd.ic = MODEL == kLinear ? 0.0 : rcp_nr(nd.c);
     }
-    // a theta(x) + sink + xi x: the part of N_i(psi) without the couplings
-    static __device__ __forceinline__ T local(const Env &e, Node &nd, T x, T &lin)
+    // N_i(psi) = a theta(x) + sink + (xi x + md), md = sum_j m_ij (x - psi_j), with
+    // the roundings apply_N_t has in the launched kernels (TILE) and had in the
+    // one-work-group cycle (compilers contract its last sum differently there)
+    template <bool TILE = false>
+    static __device__ __forceinline__ T apply(const Env &e, const Node &nd, T x, T md)
     {
-        T s;
-        if constexpr (MODEL == kMulti) s = e.a * theta_defect<kMulti>(e.soils[nd.soil], x, nd.ps);
-        else s = e.a * theta_defect<MODEL>(e.L, x, nd.ps);
+#pragma clang fp contract(off)
+        T th;
+        if constexpr (MODEL == kMulti) th = theta_only(e.soils[nd.soil], x);
+        else th = theta_only_t<MODEL>(e.L, x);
+        const T rest = fma(e.L.xi, x, md);
         if (SINK) {
             T fa, dfa;
             feddes(e.L, x, fa, dfa);
-            s += nd.b * fa;
+            return fma(e.a, th, nd.b * fa) + rest;
         }
-        lin = e.L.xi * x;
-        return s;
+        if (TILE || MODEL == kMulti) return fma(e.a, th, rest);
+        return e.a * th + rest;
     }
     static __device__ __forceinline__ T solve(const Env &e, Node &nd, T f)
     {
         if constexpr (MODEL == kMulti) {
             const Law &Ls = e.soils[nd.soil];
-            return local_solve_soil_ic<SINK, 0, true>(Ls, e.a, nd.b, nd.c, nd.ic, f, nd.x, nd.ps);
+            return local_solve_soil_ic<SINK, 0>(Ls, e.a, nd.b, nd.c, nd.ic, f, nd.x);
         } else {
-            return local_solve_ic<MODEL, SINK, 0, true, true>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x,
-                                                               nd.ps);
+            return local_solve_ic<MODEL, SINK, 0>(e.L, e.a, nd.b, nd.c, nd.ic, f, nd.x);
         }
     }
     // moved by more than 4 ulp
@@ -263,15 +249,13 @@ struct WgOp32 {
         T up, down, ab;
         int p;
     };
-    static constexpr int kKept = 0;
-    static __device__ __forceinline__ void take(Node &, const T *, int) {}
-    static __device__ __forceinline__ void keep(const Node &, T *, int) {}
     static __device__ __forceinline__ void coefficients(const Env &e, Node &nd, T mii)
     {
         nd.c = e.L.xi + nd.kap + mii;
         nd.ic = f_rcp(nd.c);
     }
-    static __device__ __forceinline__ T local(const Env &e, Node &nd, T x, T &lin)
+    template <bool TILE = false>
+    static __device__ __forceinline__ T apply(const Env &e, const Node &nd, T x, T md)
     {
         T dth, slope;
         dtheta32<MODEL>(e.L, nd.base, x, dth, slope);
@@ -281,8 +265,7 @@ struct WgOp32 {
             dfeddes32(e.L, nd.base.psi, x, da, ds);
             s += nd.b * da;
         }
-        lin = e.L.xi * x;
-        return s;
+        return s + (e.L.xi * x + md);
     }
     static __device__ __forceinline__ T solve(const Env &e, Node &nd, T f)
     {
@@ -312,10 +295,6 @@ struct WgCycle {
     int levels, nu1, nu2, nuc;
     T *x;
     const T *rhs;
-    // first level whose nodes keep their power terms in LDS between visits (the
-    // launcher sets it by the LDS there is; never the top level, whose operator
-    // the cycle's fixed point depends on: it evaluates them afresh each visit)
-    int keep_from;
     // the coarsest level takes all its sweeps, also once no value moves (the
     // sweeps of one level on their own, levels = 1)
     int all;
@@ -329,41 +308,27 @@ struct WgMems {
 };
 
 // LDS of the cycle: per level the iterate, K*, right-hand side, restricted
-// iterate (then the correction) and, FP32, the base state, or the kept power
-// terms; one defect box of the top level's size.
+// iterate (then the correction) and, FP32, the base state; one defect box of the
+// top level's size.
 template <typename T, int DIM>
-__host__ __device__ __forceinline__ int wg_words(const WgGeo &g, int s, int keep_from, int kept)
+__host__ __device__ __forceinline__ int wg_words(const WgGeo &g, int s)
 {
-    return wg_level<DIM>(g, s).size * ((sizeof(T) == 4 ? 5 : 4) + (s >= keep_from ? kept : 0));
+    return wg_level<DIM>(g, s).size * (sizeof(T) == 4 ? 5 : 4);
 }
 
+// At most 148 KB (FP64, a 2049-node column) of 160.
 template <typename T, int DIM>
-inline size_t wg_lds_bytes(const WgGeo &g, int levels, int keep_from = kWgMaxLev, int kept = 0)
+inline size_t wg_lds_bytes(const WgGeo &g, int levels)
 {
     size_t w = 0;
-    for (int s = 0; s < levels; ++s) w += (size_t)wg_words<T, DIM>(g, s, keep_from, kept);
+    for (int s = 0; s < levels; ++s) w += (size_t)wg_words<T, DIM>(g, s);
     return sizeof(T) * (w + (size_t)wg_level<DIM>(g, 0).size);
-}
-
-// LDS for the cycle's boxes (of 160 KB, less a soil table).
-constexpr size_t kWgLds = 150 * 1024;
-
-// keep_from by the LDS there is; the bytes to launch with.
-template <typename T, int DIM>
-inline size_t wg_fit(WgCycle<T> *A, int kept)
-{
-    A->keep_from = kWgMaxLev;
-    for (int k = A->levels - 1; k >= 1 && kept > 0; --k) {
-        if (wg_lds_bytes<T, DIM>(A->g, A->levels, k, kept) > kWgLds) break;
-        A->keep_from = k;
-    }
-    return wg_lds_bytes<T, DIM>(A->g, A->levels, A->keep_from, kept);
 }
 
 template <typename T, int DIM>
 struct WgBox {
     T *x, *K, *g, *bar;
-    T *pb;   // FP32: base state; FP64: kept power terms
+    T *pb;   // FP32: base state
 };
 
 template <typename T, int DIM>
@@ -413,7 +378,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
     const WgLevel<DIM> v = wg_level<DIM>(g, s);
     const WgBox<T, DIM> B = wg_box<T, DIM>(lds, off, v);
     const WgLevel<DIM> vc = wg_level<DIM>(g, s + 1);
-    const int noff = off + wg_words<T, DIM>(g, s, A.keep_from, Op::kKept);
+    const int noff = off + wg_words<T, DIM>(g, s);
     const WgBox<T, DIM> C = wg_box<T, DIM>(lds, noff, vc);
     const bool last = s == A.levels - 1;
     const int tid = threadIdx.x;
@@ -446,9 +411,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                 q.b = Op::SINK ? (T)M.beta[c[col][u][DIM - 1]] : T(0);
                 if constexpr (sizeof(T) == 8) {
                     q.soil = 0;
-                    q.ps = kept_none();
                     if constexpr (Op::MODEL == kMulti) q.soil = M.soil[wg_mem<DIM>(g, v, c[col][u])];
-                    if (s >= A.keep_from) Op::take(q, B.pb, v.size);
                 } else {
                     q.base.psi = B.pb[q.p];
                 }
@@ -543,13 +506,11 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
                     typename Op::Node &q = nd[col][u];
-                    T lin1;
-                    const T loc = Op::local(e, q, q.x, lin1);
                     T md = T(0);
 #pragma unroll
                     for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - bn[col][u][t]);
                     if (on[col][u]) {
-                        q.g = (loc + (lin1 + md)) + q.g;
+                        q.g = Op::apply(e, q, q.x, md) + q.g;
                         B.g[q.p] = q.g;
                     }
                 }
@@ -588,7 +549,6 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
             }
         }
     }
-    const bool keep = s >= A.keep_from;
     if (!up && !last && !norm_only) {
         // defect (0 at Dirichlet nodes), then its full weighting and the iterate's
         {
@@ -605,13 +565,10 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
                     typename Op::Node &q = nd[col][u];
-                    T lin1;
-                    const T loc = Op::local(e, q, q.x, lin1);
                     T md = T(0);
 #pragma unroll
                     for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - xn[col][u][t]);
-                    if (has[col][u]) dbox[q.p] = on[col][u] ? q.g - (loc + (lin1 + md)) : T(0);
-                    if (keep && has[col][u]) Op::keep(q, B.pb, v.size);
+                    if (has[col][u]) dbox[q.p] = on[col][u] ? q.g - Op::apply(e, q, q.x, md) : T(0);
                 }
         }
         wg_sync<WAVE>();
@@ -669,10 +626,8 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
         for (int col = 0; col < 2; ++col)
 #pragma unroll
             for (int u = 0; u < S; ++u)
-                if (has[col][u]) {
+                if (has[col][u])
                     B.bar[nd[col][u].p] = nd[col][u].x - B.bar[nd[col][u].p];
-                    if (keep) Op::keep(nd[col][u], B.pb, v.size);
-                }
         wg_sync<WAVE>();
     } else if (norm) {
         double m = 0.0;
@@ -681,12 +636,10 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
 #pragma unroll
             for (int u = 0; u < S; ++u) {
                 typename Op::Node &q = nd[col][u];
-                T lin1;
-                const T loc = Op::local(e, q, q.x, lin1);
                 T md = T(0);
 #pragma unroll
                 for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - B.x[q.p + so[t]]);
-                const double r = on[col][u] ? fabs((double)(q.g - (loc + (lin1 + md)))) : 0.0;
+                const double r = on[col][u] ? fabs((double)(q.g - Op::apply(e, q, q.x, md))) : 0.0;
                 m = (r > m || r != r) ? r : m;
             }
         if (WAVE) {
@@ -724,7 +677,7 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
     // right-hand side; zeros elsewhere.  The loads of all levels that a pass of
     // the work-group covers are in flight together.
     int total = 0;
-    for (int s = 0; s < A.levels; ++s) total += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+    for (int s = 0; s < A.levels; ++s) total += wg_words<T, DIM>(A.g, s);
     T *dbox = lds + total;
     const int all = total + wg_level<DIM>(A.g, 0).size;
     for (int t = tid; t < all; t += nthreads) lds[t] = T(0);
@@ -753,7 +706,7 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
                 B.K[wg_pos<DIM>(v, c)] = k0[s];
                 if (sizeof(T) == 4) B.pb[wg_pos<DIM>(v, c)] = p0[s];
             }
-            off += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+            off += wg_words<T, DIM>(A.g, s);
         }
     off = 0;
     for (int s = 0; s < A.levels; ++s) {
@@ -775,7 +728,7 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
                 B.g[p] = A.rhs[at];
             }
         }
-        off += wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+        off += wg_words<T, DIM>(A.g, s);
     }
     __syncthreads();
     return dbox;
@@ -821,7 +774,7 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
     for (int q = 0; q < visits; ++q) {
         const bool up = q >= A.levels;
         const int s = up ? visits - 1 - q : q;
-        const int words = wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+        const int words = wg_words<T, DIM>(A.g, s);
         if (up) off -= words;
         wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, nullptr, false);
         if (!up && s + 1 < A.levels) off += words;
@@ -864,7 +817,7 @@ __device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const
     while (true) {
         const bool up = q >= A.levels;
         const int s = q < 0 ? 0 : (up ? visits - 1 - q : q);
-        const int words = wg_words<T, DIM>(A.g, s, A.keep_from, Op::kKept);
+        const int words = wg_words<T, DIM>(A.g, s);
         if (up) off -= words;
         const bool end = q < 0 || q == visits - 1;
         wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, end ? &norm : nullptr, q < 0);

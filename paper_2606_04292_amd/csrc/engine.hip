@@ -661,8 +661,7 @@ __global__ __launch_bounds__(kWgMaxThreads) void e_tail(const EList *__restrict_
         __syncthreads();
     }
     if (wg <= last) {
-        const WgCycle<float> A{S.wg_geo, last - wg + 1, nu1, nu2, nuc, LV[wg].dl, LV[wg].rhs,
-                               kWgMaxLev};
+        const WgCycle<float> A{S.wg_geo, last - wg + 1, nu1, nu2, nuc, LV[wg].dl, LV[wg].rhs};
         const SlotMems M{LV + wg};
         const Law32 law = S.law32;
         law_dim(law.model, LV[0].geo.dim, [&](auto Mo, auto Dm) {

@@ -51,11 +51,10 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_solve_wg(WgCycle<double> A, W
 
 // A.nuc sweeps of one level: the visit of the cycle's coarsest one, with no sweep
 // left out.  Bound by the chain of barriers and solves of one work-group, so the
-// level is loaded once and its nodes, face coefficients and power terms stay in
-// registers.  Against the kernel before it (global loads and a division per node
-// and sweep), two and twenty sweeps: 65 nodes 7.7 -> 6.0 and 55 -> 21 us, 513
-// nodes 15.2 -> 7.3 and 130 -> 32, 9^3 22.5 -> 9.4 and 203 -> 39 (vGM); against
-// one launch per colour 1025 nodes 18.6 -> 8.9 and 166 -> 40.
+// level is loaded once and its nodes and face coefficients stay in registers.
+// Against one launch per colour, two and twenty sweeps: 1025 nodes 19.2 -> 9.9 and
+// 169 -> 61 us, 33^2 21.2 -> 11.6 and 181 -> 71, 9x9x17 21.3 -> 12.8 and 181 -> 73
+// (vGM).
 template <int MODEL, bool SINK, int DIM>
 __global__ __launch_bounds__(kWgMaxThreads) void k_sweeps_wg(WgCycle<double> A, WgMems<double> M,
                                                              Law L, double a)
@@ -65,7 +64,6 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_sweeps_wg(WgCycle<double> A, 
     typedef WgOp64<MODEL, SINK, DIM> Op;
     const typename Op::Env e{L, soils, a};
     A.levels = 1;   // known here: the transfers drop out of the visit's code
-    A.keep_from = kWgMaxLev;
     A.all = 1;
     double *dbox = wg_load<Op>(A, M, lds64);
     bool wave = false;
@@ -88,12 +86,11 @@ struct CycleWgLaunch {
     template <int MO, bool S, int D>
     void go()
     {
-        WgCycle<double> C = A;
-        const size_t bytes = wg_fit<double, D>(&C, WgOp64<MO, false, D>::kKept);
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
         if (bytes > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C, M,
+        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
                            law, a);
     }
 };
@@ -118,12 +115,11 @@ struct SolveWgLaunch {
     template <int MO, bool SK, int D>
     void go()
     {
-        WgCycle<double> C = A;
-        const size_t bytes = wg_fit<double, D>(&C, WgOp64<MO, false, D>::kKept);
+        const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
         if (bytes > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)k_solve_wg<MO, SK, D>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_solve_wg<MO, SK, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C,
+        hipLaunchKernelGGL((k_solve_wg<MO, SK, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
                            M, law, a, S, out);
     }
 };

@@ -37,12 +37,11 @@ struct CycleWg32Launch {
     template <int MO, bool S, int D>
     void go()
     {
-        WgCycle<float> C = A;
-        const size_t bytes = wg_fit<float, D>(&C, 0);
+        const size_t bytes = wg_lds_bytes<float, D>(A.g, A.levels);
         if (bytes > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)k_cycle_wg32<MO, S, D>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg32<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, C,
+        hipLaunchKernelGGL((k_cycle_wg32<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
                            M, law, a);
     }
 };

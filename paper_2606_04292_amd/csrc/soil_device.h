@@ -222,100 +222,6 @@ __device__ __forceinline__ ThetaEval theta_next(const Law &L, double x, PowState
     return r;
 }
 
-// Power terms of the last law evaluation at a node.
-struct PowKept {
-    bool ok;       // the last iterate was unsaturated (Haverkamp, vGM)
-    double h;      // its magnitude: unit |x| (Haverkamp), |x| (vGM)
-    double ih;     // 1 / h
-    double q;      // Haverkamp: Q = (unit |x|)^beta; vGM: P = (alpha |x|)^n
-    double se;     // vGM: Se = (1 + P)^-m
-    double ix1p;   // vGM: 1 / (1 + P)
-};
-
-// The state behind a magnitude and the vGM power terms that were kept (h = 0:
-// none).
-__device__ __forceinline__ PowKept pow_kept(double h, double q, double se)
-{
-    const double X = 1.0 + q, w = rcp_1nr(X * h);
-    return PowKept{h > 0.0, h, X * w, q, se, h * w};
-}
-
-__device__ __forceinline__ PowKept kept_none()
-{
-    return PowKept{false, 0.0, 0.0, 0.0, 1.0, 0.0};
-}
-
-// The law at x < 0 within the visits of one node: theta - theta_r = L.c_th s and
-// theta' = law_slope(L) ds.  The power terms of the Haverkamp and vGM laws scale from
-// the last iterate's: Q(x) = Q(x') (1 + u)^beta and P(x) = P(x') (1 + u)^n with
-// u = x / x' - 1, then Se(x) = Se(x') (1 + v)^-m with v = (P(x) - P(x')) / (1 + P(x'));
-// each factor is taken by the binomial series while its u or v is below
-// L.series_u (2^-8; 0 for exponents outside [-1, 7]) in magnitude, else the
-// powers are evaluated afresh.  A scaled power adds one rounding to the last
-// one's error (the argument u carries |u| times its own), far below the few ulp
-// times the exponent of a fresh evaluation.  NR2: two Newton-Raphson steps in
-// the reciprocal that enters theta, for values that enter a defect.
-template <int MODEL, bool NR2 = false>
-__device__ __forceinline__ void law_unsat(const Law &L, double x, PowKept &p, double &s,
-                                          double &ds)
-{
-    if (MODEL == kLinear) {
-        s = x;
-        ds = 1.0;
-    } else if (MODEL == kGardner) {
-        s = rs_exp(L.gd_alpha * L.unit * x);
-        ds = s;
-    } else if (MODEL == kHaverkamp) {
-        const double hu = -L.unit * x;
-        const double u = (hu - p.h) * p.ih;
-        double Q;
-        if (p.ok && fabs(u) < L.series_u) Q = fma(p.q, pow1p_m1_series(u, L.bin1), p.q);
-        else Q = rs_exp(L.hk_beta * rs_log(hu));
-        // one reciprocal serves 1/(alpha + Q) = hu w and 1/hu = (alpha + Q) w
-        const double den = L.hk_alpha + Q;
-        const double w = NR2 ? rcp_nr(hu * den) : rcp_1nr(hu * den);
-        s = hu * w;
-        ds = Q * (s * w);
-        p.q = Q;
-        p.h = hu;
-        p.ih = den * w;
-        p.ok = true;
-    } else {
-        const double h = -x;
-        const double u = (h - p.h) * p.ih;
-        double P = 0.0;
-        bool fresh = true;
-        if (p.ok && fabs(u) < L.series_u) {
-            const double dP = p.q * pow1p_m1_series(u, L.bin1);
-            const double v = dP * p.ix1p;
-            P = p.q + dP;
-            if (fabs(v) < L.series_u) {
-                s = fma(p.se, pow1p_m1_series(v, L.bin2), p.se);
-                fresh = false;
-            }
-        }
-        if (fresh) {
-            P = rs_exp(L.vg_n * rs_log(L.vg_alpha * h));
-            s = rs_exp(-L.vg_m * rs_log1p(P));
-        }
-        const double X = 1.0 + P;
-        const double w = rcp_1nr(X * h);
-        ds = P * (s * w);
-        p.q = P;
-        p.se = s;
-        p.h = h;
-        p.ih = X * w;
-        p.ix1p = h * w;
-        p.ok = true;
-    }
-}
-
-template <int MODEL>
-__device__ __forceinline__ double law_slope(const Law &L)
-{
-    return MODEL == kHaverkamp ? L.c_dth * L.c_th : L.c_dth;
-}
-
 template <int MODEL>
 __device__ __forceinline__ double theta_only_t(const Law &L, double x)
 {
@@ -370,39 +276,6 @@ __device__ __forceinline__ void feddes(const Law &L, double x, double &a, double
     else { a = 0.0; da = 0.0; }
 }
 
-// law_unsat where every active lane of the wave is unsaturated and within the
-// series' range of its last evaluation; false (and nothing done) otherwise.
-template <int MODEL>
-__device__ __forceinline__ bool law_scaled(const Law &L, double x, PowKept &p, double &s,
-                                           double &ds)
-{
-    const double h = MODEL == kHaverkamp ? -L.unit * x : -x;
-    const double u = (h - p.h) * p.ih;
-    const double dq = p.q * pow1p_m1_series(u, L.bin1);
-    bool good = p.ok & (x < 0.0) & (fabs(u) < L.series_u);
-    const double v = dq * p.ix1p;
-    if (MODEL == kVgm) good = good & (fabs(v) < L.series_u);
-    if (__builtin_amdgcn_ballot_w64(!good) != 0) return false;
-    p.q += dq;
-    p.h = h;
-    if (MODEL == kHaverkamp) {
-        const double den = L.hk_alpha + p.q;
-        const double w = rcp_1nr(h * den);
-        s = h * w;
-        ds = p.q * (s * w);
-        p.ih = den * w;
-    } else {
-        s = fma(p.se, pow1p_m1_series(v, L.bin2), p.se);
-        const double X = 1.0 + p.q;
-        const double w = rcp_1nr(X * h);
-        ds = p.q * (s * w);
-        p.se = s;
-        p.ih = X * w;
-        p.ix1p = h * w;
-    }
-    return true;
-}
-
 // Pointwise equation of the NGS update (eq. point-update with the BDF
 // coefficient a and sink beta * a_F):  a theta(x) + beta a_F(x) + c x = f.
 // NEWTON (or L.newton when NEWTON == 0) safeguarded Newton steps from x0: the
@@ -420,11 +293,9 @@ __device__ __forceinline__ bool law_scaled(const Law &L, double x, PowKept &p, d
 // terms, a (theta_r + ...): a product of a and the law's scale rounded once for the
 // whole grid (one instruction less) moved the fixed point of every node one way,
 // by up to 2 half-ulps of psi.
-// KEPT: pk holds the node's last evaluation (WAVE: scaled without a branch per lane
-// where the whole wave is close to it).
-template <int MODEL, bool SINK, int NEWTON, bool KEPT = false, bool WAVE = false>
+template <int MODEL, bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double beta, double c,
-                                                 double ic, double f, double x0, PowKept &pk)
+                                                 double ic, double f, double x0)
 {
     double lo, hi;
     if (MODEL == kLinear) {
@@ -446,24 +317,7 @@ __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double 
     const int iters = NEWTON > 0 ? NEWTON : L.newton;
 #pragma clang loop unroll_count(NEWTON == 3 && MODEL == kHaverkamp ? 3 : 1)
     for (int k = 0; k < iters; ++k) {
-        ThetaEval t;
-        if constexpr (KEPT) {
-            double s = 0.0, ds = 0.0;
-            bool near = false;
-            if constexpr (WAVE && (MODEL == kHaverkamp || MODEL == kVgm))
-                near = law_scaled<MODEL>(L, x, pk, s, ds);
-            t.th = L.ts;   // saturated
-            t.dth = 0.0;
-            if (near || MODEL == kLinear || x < 0.0) {
-                if (!near) law_unsat<MODEL>(L, x, pk, s, ds);
-                t.th = L.tr + L.c_th * s;
-                t.dth = law_slope<MODEL>(L) * ds;
-            } else {
-                pk.ok = false;
-            }
-        } else {
-            t = theta_next<MODEL>(L, x, ps);
-        }
+        const ThetaEval t = theta_next<MODEL>(L, x, ps);
         double F = fma(c, x, a * t.th) - f;
         double dF = fma(a, t.dth, c);
         if (SINK) {
@@ -494,23 +348,21 @@ template <int MODEL, bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_t(const Law &L, double a, double beta, double c,
                                                 double f, double x0)
 {
-    PowKept pk = kept_none();
     return local_solve_ic<MODEL, SINK, NEWTON>(L, a, beta, c, MODEL == kLinear ? 0.0 : rcp_nr(c),
-                                               f, x0, pk);
+                                               f, x0);
 }
 
 // The pointwise solve with the law of one soil picked at run time (layered
 // media): the same iteration as local_solve_t for that soil's model.
-template <bool SINK, int NEWTON, bool KEPT = false>
+template <bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_soil_ic(const Law &Ls, double a, double beta,
-                                                      double c, double ic, double f, double x0,
-                                                      PowKept &pk)
+                                                      double c, double ic, double f, double x0)
 {
     switch (Ls.model) {
-    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
-    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
-    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
-    default: return local_solve_ic<kLinear, SINK, NEWTON, KEPT>(Ls, a, beta, c, ic, f, x0, pk);
+    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
+    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
+    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
+    default: return local_solve_ic<kLinear, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
     }
 }
 
@@ -518,31 +370,7 @@ template <bool SINK, int NEWTON>
 __device__ __forceinline__ double local_solve_soil(const Law &Ls, double a, double beta, double c,
                                                    double f, double x0)
 {
-    PowKept pk = kept_none();
-    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0, pk);
-}
-
-// theta at x for a defect, from the power terms of the node's last evaluation.
-template <int MODEL>
-__device__ __forceinline__ double theta_defect(const Law &L, double x, PowKept &ps)
-{
-    if constexpr (MODEL == kMulti) {
-        switch (L.model) {
-        case kHaverkamp: return theta_defect<kHaverkamp>(L, x, ps);
-        case kVgm: return theta_defect<kVgm>(L, x, ps);
-        default: return theta_only(L, x);
-        }
-    } else if constexpr (MODEL == kHaverkamp || MODEL == kVgm) {
-        if (!(x < 0.0)) {
-            ps.ok = false;
-            return L.ts;
-        }
-        double s, ds;
-        law_unsat<MODEL, true>(L, x, ps, s, ds);
-        return L.tr + L.c_th * s;
-    } else {
-        return theta_only_t<MODEL>(L, x);
-    }
+    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0);
 }
 
 // Node kinds from indices (no node-type array): Dirichlet if on a Dirichlet
