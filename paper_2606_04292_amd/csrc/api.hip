@@ -262,6 +262,7 @@ struct rs_grid {
     hipEvent_t norm_ev;               // a norm has reached host_bits (with host_dev)
     Law *soil_tab;                    // device table of per-soil laws (layered media)
     int tail_top;                     // first level of the one-work-group cycle (nlev: none)
+    int tiles;                        // bit l: level l runs in tiles (route_levels)
     Law law;
     Law32 law32;
     bool law_set;
@@ -671,16 +672,25 @@ double wg_updates(const rs_grid *G, int l, int nu1, int nu2);
 // launches.
 constexpr long long kTileMaxNodes = 1ll << 17;
 
-bool tile_level(const rs_grid *G, int l)
+// Which levels do is decided once, at the entry of a call that runs cycles: the
+// parts of one cycle have to agree (a tiled way down leaves the smoothed iterate
+// in the level's second array and the coarse level ready, a plain one its defect
+// there), also where a part is captured into a graph with the profiling events
+// off or the environment changes meanwhile.
+void route_levels(rs_grid *G)
 {
-    const Geo &g = G->lev[l].geo;
-    if (g.dim > 2 || l >= G->tail_top || l >= G->nlev - 1 || G->lev[l].psi_alt ||
-        g.N > kTileMaxNodes || (l == 0 && G->prof_on) || getenv("RS_SWEEP"))
-        return false;
-    // the smallest halo of a sweep and of a transfer with one sweep fit
-    int own[2], tiles[2];
-    return tile_shape(g, 6, own, tiles);
+    G->tiles = 0;
+    if (getenv("RS_SWEEP")) return;
+    for (int l = G->prof_on ? 1 : 0; l < G->tail_top && l < G->nlev - 1; ++l) {
+        const Geo &g = G->lev[l].geo;
+        // the smallest halo of a sweep and of a transfer with one sweep fit
+        int own[2], tiles[2];
+        if (g.dim <= 2 && !G->lev[l].psi_alt && g.N <= kTileMaxNodes && tile_shape(g, 6, own, tiles))
+            G->tiles |= 1 << l;
+    }
 }
+
+bool tile_level(const rs_grid *G, int l) { return (G->tiles >> l) & 1; }
 
 // One launch of a tiled phase with ns sweeps: its halo, tiles, and an estimate
 // of its time in us (12 to 15 measured for a launch with four colour passes on
@@ -893,10 +903,8 @@ int coarse_cycle(rs_grid *G, int which, int nu1, int nu2)
     k.nu2 = nu2;
     k.nu_coarse = G->nu_coarse;
     k.law_version = G->law_version;
-    for (int l = 0; l < G->nlev; ++l) {
-        k.lambdaU[l] = G->lev[l].lambdaU;
-        k.tiles |= (tile_level(G, l) ? 1 : 0) << l;
-    }
+    for (int l = 0; l < G->nlev; ++l) k.lambdaU[l] = G->lev[l].lambdaU;
+    k.tiles = G->tiles;
     if (!G->cg[which] || memcmp(&k, G->cg_key[which], sizeof k) != 0) {
         if (G->cg[which]) {
             HIPCALL(hipStreamSynchronize(G->stream));   // a replay may still run
@@ -1412,6 +1420,7 @@ int rs_vcycle(rs_grid *G, int nu1, int nu2, double *res)
     if (!G) return fail(RS_EINVAL, "null grid");
     if (!G->in_step) return fail(RS_ESTATE, "no active step (call rs_begin_step)");
     if (nu1 < 0 || nu2 < 0) return fail(RS_EINVAL, "negative smoothing count");
+    route_levels(G);
     int e = vcycle_level(G, 0, nu1, nu2);
     if (e) return e;
     HIPCALL(hipGetLastError());
@@ -1424,6 +1433,7 @@ int rs_fmg(rs_grid *G, int nu1, int nu2, double *res)
     if (!G) return fail(RS_EINVAL, "null grid");
     if (!G->in_step) return fail(RS_ESTATE, "no active step (call rs_begin_step)");
     if (nu1 < 0 || nu2 < 0) return fail(RS_EINVAL, "negative smoothing count");
+    route_levels(G);
     int e = fmg_cycle(G, nu1, nu2);
     if (e) return e;
     HIPCALL(hipGetLastError());
@@ -1437,6 +1447,7 @@ int rs_correction_cycle(rs_grid *G, int inner_cycles, int nu1, int nu2, double *
     if (G->precision != RS_MIXED) return fail(RS_ESTATE, "grid was not created with RS_MIXED");
     if (!G->in_step) return fail(RS_ESTATE, "no active step (call rs_begin_step)");
     if (inner_cycles < 1 || nu1 < 0 || nu2 < 0) return fail(RS_EINVAL, "bad cycle counts");
+    route_levels(G);
     double r;
     int e = fine_norm(G, &r, nullptr, true);
     if (e) return e;
@@ -1494,6 +1505,7 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     if (o->nu1 < 0 || o->nu2 < 0 || o->nu_coarse < 1 || o->max_cycles < 0)
         return fail(RS_EINVAL, "bad solve options");
     G->nu_coarse = o->nu_coarse;
+    route_levels(G);
     int e = rs_begin_step(G, dt, order);
     if (e) return e;
     const bool mixed = G->precision == RS_MIXED;
