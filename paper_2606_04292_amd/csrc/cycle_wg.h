@@ -199,9 +199,9 @@ struct WgOp64 {
         nd.ic = MODEL == kLinear ? 0.0 : rcp_nr(nd.c);
     }
     // N_i(psi) = a theta(x) + sink + (xi x + md), md = sum_j m_ij (x - psi_j), with
-    // the roundings apply_N_t has in the launched kernels (TILE) and had in the
-    // one-work-group cycle (compilers contract its last sum differently there)
-    template <bool TILE = false>
+    // the roundings apply_N_t has in the launched kernels (LAUNCHED: tiles, norms)
+    // and had in the one-work-group cycle (its last sum contracts differently there)
+    template <bool LAUNCHED = false>
     static __device__ __forceinline__ T apply(const Env &e, const Node &nd, T x, T md)
     {
 #pragma clang fp contract(off)
@@ -214,7 +214,7 @@ struct WgOp64 {
             feddes(e.L, x, fa, dfa);
             return fma(e.a, th, nd.b * fa) + rest;
         }
-        if (TILE || MODEL == kMulti) return fma(e.a, th, rest);
+        if (LAUNCHED || MODEL == kMulti) return fma(e.a, th, rest);
         return e.a * th + rest;
     }
     static __device__ __forceinline__ T solve(const Env &e, Node &nd, T f)
@@ -254,7 +254,7 @@ struct WgOp32 {
         nd.c = e.L.xi + nd.kap + mii;
         nd.ic = f_rcp(nd.c);
     }
-    template <bool TILE = false>
+    template <bool LAUNCHED = false>
     static __device__ __forceinline__ T apply(const Env &e, const Node &nd, T x, T md)
     {
         T dth, slope;
@@ -639,7 +639,7 @@ __device__ __forceinline__ void wg_visit(const WgCycle<typename Op::T> &A,
                 T md = T(0);
 #pragma unroll
                 for (int t = 0; t < NQ; ++t) md += q.m[t] * (q.x - B.x[q.p + so[t]]);
-                const double r = on[col][u] ? fabs((double)(q.g - Op::apply(e, q, q.x, md))) : 0.0;
+                const double r = on[col][u] ? fabs((double)(q.g - Op::template apply<true>(e, q, q.x, md))) : 0.0;
                 m = (r > m || r != r) ? r : m;
             }
         if (WAVE) {

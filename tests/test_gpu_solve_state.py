@@ -64,6 +64,8 @@ def test_the_cycles_of_a_step_are_those_of_vcycle_calls(name, cycles):
     # (a defect of exactly zero ends the step before)
     done = st.cycles
     x = np_(G.psi() if code == rsl.RS_ENOTCONV else G.get_state()[0])
+    if code == rsl.RS_ENOTCONV:   # the norm reported is that of the iterate left
+        assert st.res == G.residual_norm()
     assert (code == rsl.RS_ENOTCONV and done == cycles) or (code == rsl.RS_OK and st.res == 0.0)
     G.close()
     G = rsl.Grid(w)
