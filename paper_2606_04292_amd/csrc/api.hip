@@ -1176,7 +1176,7 @@ void grid_view(rs_grid *G, const rs_grid_desc *d, int precision, const Layout &L
     G->prof_cells = 0.0;
     G->host_bits = host_bits;
     G->tail_top = G->nlev;
-    for (int l = G->nlev - 1; l >= 0 && wg_level_fits(G->lev[l].geo) && !G->lev[l].psi_alt;
+    for (int l = G->nlev - 1; l >= 0 && wg_cycle_level(G->lev[l].geo) && !G->lev[l].psi_alt;
          --l)
         G->tail_top = l;
 }
@@ -1532,7 +1532,8 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     };
     // FP64 grids that fit one work-group run their cycles and the stopping test
     // in it, kWgSolveCycles to a launch.
-    const bool whole = !mixed && G->nlev > 1 && G->tail_top == 0 && G->host_dev;
+    const bool whole = !mixed && G->nlev > 1 && G->tail_top == 0 && G->host_dev &&
+                       wg_level_fits(G->lev[0].geo);
     double r = 0.0, r0 = 0.0, best = 0.0;
     int cycles = 0, slow = 0, nh = 0;
     double hist[64];

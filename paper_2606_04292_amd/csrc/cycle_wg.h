@@ -38,8 +38,8 @@ namespace rs {
 constexpr int kWgMaxLev = 12;        // levels of one cycle (2049 nodes on the shortest axis)
 // Cycles of one launch of the whole-grid solve (a few milliseconds at most).
 constexpr int kWgSolveCycles = 60;
-// Three waves per SIMD, so a lane may hold 168 registers (2-D and 3-D levels
-// take one node per thread and colour; with two the 3-D kernels spilled).
+// Three waves per SIMD, so a lane may hold 168 registers (2-D and most 3-D levels
+// take one node per thread and colour; with two the 3-D kernels spill).
 constexpr int kWgMaxThreads = 768;
 
 // The geometry of the cycle's top level that the kernels read (few scalars).
@@ -734,10 +734,10 @@ __device__ __forceinline__ typename Op::T *wg_load(const WgCycle<typename Op::T>
     return dbox;
 }
 
-// One visit, in the mode of its level: two nodes per thread and colour on 1-D
-// levels of more than kWgMaxThreads nodes per colour, one wave from the first
-// level of at most 64 nodes per colour (wave: the last visit was of that kind).
-template <class Op, class Mem>
+// One visit, in the mode of its level: two nodes per thread and colour on levels
+// of more nodes per colour than threads (TWO), one wave from the first level of
+// at most 64 nodes per colour (wave: the last visit was of that kind).
+template <class Op, bool TWO, class Mem>
 __device__ __forceinline__ void wg_visit_mode(const WgCycle<typename Op::T> &A, const Mem &mem,
                                               const typename Op::Env &e, int s, bool up,
                                               bool &wave, typename Op::T *lds, int off,
@@ -756,12 +756,12 @@ __device__ __forceinline__ void wg_visit_mode(const WgCycle<typename Op::T> &A, 
     wave = false;
     if (slots <= nthreads)
         wg_visit<Op, 1, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox, norm, norm_only);
-    else if constexpr (DIM == 1)
+    else if constexpr (TWO)
         wg_visit<Op, 2, false>(A, mem(s), e, s, up, nthreads, lds, off, dbox, norm, norm_only);
 }
 
 // The cycle: down and up over the levels.
-template <class Op, class Mem>
+template <class Op, bool TWO = Op::DIM == 1, class Mem>
 __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const Mem &mem,
                                          const typename Op::Env &e, typename Op::T *lds)
 {
@@ -776,7 +776,7 @@ __device__ __forceinline__ void wg_cycle(const WgCycle<typename Op::T> &A, const
         const int s = up ? visits - 1 - q : q;
         const int words = wg_words<T, DIM>(A.g, s);
         if (up) off -= words;
-        wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, nullptr, false);
+        wg_visit_mode<Op, TWO>(A, mem, e, s, up, wave, lds, off, dbox, nullptr, false);
         if (!up && s + 1 < A.levels) off += words;
     }
 }
@@ -820,7 +820,8 @@ __device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const
         const int words = wg_words<T, DIM>(A.g, s);
         if (up) off -= words;
         const bool end = q < 0 || q == visits - 1;
-        wg_visit_mode<Op>(A, mem, e, s, up, wave, lds, off, dbox, end ? &norm : nullptr, q < 0);
+        wg_visit_mode<Op, DIM == 1>(A, mem, e, s, up, wave, lds, off, dbox, end ? &norm : nullptr,
+                                    q < 0);
         if (!end) {
             if (!up && s + 1 < A.levels) off += words;
             ++q;
@@ -868,10 +869,20 @@ __device__ __forceinline__ void wg_solve(const WgCycle<typename Op::T> &A, const
     }
 }
 
-// Levels that fit the work-group.
+// Levels that fit the work-group, with two nodes per thread and colour in 1-D only.
 inline bool wg_level_fits(const Geo &g)
 {
     return g.N <= (g.dim == 1 ? kTailNodes : 2LL * kWgMaxThreads);
+}
+
+// Levels of a grid's V-cycles that run in it: also the 3-D ones up to kTailNodes
+// nodes (5x5x65 and its like), two nodes per thread and colour, in a kernel of
+// their own (in the others' it would cost registers).  A V(2,2) cycle of 5x5x65
+// nodes, launches per colour and transfer against this: 104 us (vGM) and 99
+// (Haverkamp) against 47 and 90, in mixed precision 207 and 234 against 100 and 95.
+inline bool wg_cycle_level(const Geo &g)
+{
+    return wg_level_fits(g) || (g.dim == 3 && g.N <= kTailNodes);
 }
 
 // Work-group size: one node per thread and colour on the top level where that

@@ -27,14 +27,14 @@ __device__ __forceinline__ const Law *stage_soils(const Law &L)
 
 // The V-cycle from a level of at most kTailNodes nodes down and back in one
 // work-group (cycle_wg.h).
-template <int MODEL, bool SINK, int DIM>
+template <int MODEL, bool SINK, int DIM, bool TWO>
 __global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg(WgCycle<double> A, WgMems<double> M,
                                                             Law L, double a)
 {
     extern __shared__ double lds64[];
     const Law *soils = stage_soils<MODEL>(L);
     typedef WgOp64<MODEL, SINK, DIM> Op;
-    wg_cycle<Op>(A, M, typename Op::Env{L, soils, a}, lds64);
+    wg_cycle<Op, TWO>(A, M, typename Op::Env{L, soils, a}, lds64);
 }
 
 // The cycles of a step on a grid whose finest level fits one work-group.
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_sweeps_wg(WgCycle<double> A, 
     A.all = 1;
     double *dbox = wg_load<Op>(A, M, lds64);
     bool wave = false;
-    wg_visit_mode<Op>(A, M, e, 0, false, wave, lds64, 0, dbox, nullptr, false);
+    wg_visit_mode<Op, DIM == 1>(A, M, e, 0, false, wave, lds64, 0, dbox, nullptr, false);
 }
 
 // One tile of a phase of a level (cycle_tile.h).
@@ -83,15 +83,22 @@ __global__ __launch_bounds__(kTileThreads) void k_cycle_tile(TileArgs<double> A,
 
 struct CycleWgLaunch {
     const WgCycle<double> &A; const WgMems<double> &M; const Law &law; double a; hipStream_t s;
-    template <int MO, bool S, int D>
-    void go()
+    template <int MO, bool S, int D, bool TWO>
+    void run()
     {
         const size_t bytes = wg_lds_bytes<double, D>(A.g, A.levels);
         if (bytes > 64 * 1024)
-            (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D>,
+            (void)hipFuncSetAttribute((const void *)k_cycle_wg<MO, S, D, TWO>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A, M,
-                           law, a);
+        hipLaunchKernelGGL((k_cycle_wg<MO, S, D, TWO>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
+                           M, law, a);
+    }
+    template <int MO, bool S, int D>
+    void go()
+    {
+        if constexpr (D == 3)
+            if (A.g.n[0] * A.g.n[1] * A.g.n[2] > 2 * kWgMaxThreads) return run<MO, S, D, true>();
+        run<MO, S, D, D == 1>();
     }
 };
 

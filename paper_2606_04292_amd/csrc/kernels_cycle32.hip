@@ -13,13 +13,13 @@ namespace {
 
 // The FP32 correction cycle from a level of at most kTailNodes nodes down and
 // back in one work-group (cycle_wg.h).
-template <int MODEL, bool SINK, int DIM>
+template <int MODEL, bool SINK, int DIM, bool TWO>
 __global__ __launch_bounds__(kWgMaxThreads) void k_cycle_wg32(WgCycle<float> A, WgMems<float> M,
                                                               Law32 L, float a)
 {
     extern __shared__ float lds32[];
     typedef WgOp32<MODEL, SINK, DIM> Op;
-    wg_cycle<Op>(A, M, typename Op::Env{L, a}, lds32);
+    wg_cycle<Op, TWO>(A, M, typename Op::Env{L, a}, lds32);
 }
 
 // One tile of a phase of a level (cycle_tile.h).
@@ -34,15 +34,22 @@ __global__ __launch_bounds__(kTileThreads) void k_cycle_tile32(TileArgs<float> A
 
 struct CycleWg32Launch {
     const WgCycle<float> &A; const WgMems<float> &M; const Law32 &law; float a; hipStream_t s;
-    template <int MO, bool S, int D>
-    void go()
+    template <int MO, bool S, int D, bool TWO>
+    void run()
     {
         const size_t bytes = wg_lds_bytes<float, D>(A.g, A.levels);
         if (bytes > 64 * 1024)
-            (void)hipFuncSetAttribute((const void *)k_cycle_wg32<MO, S, D>,
+            (void)hipFuncSetAttribute((const void *)k_cycle_wg32<MO, S, D, TWO>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        hipLaunchKernelGGL((k_cycle_wg32<MO, S, D>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
+        hipLaunchKernelGGL((k_cycle_wg32<MO, S, D, TWO>), dim3(1), dim3(wg_threads(A.g, D)), bytes, s, A,
                            M, law, a);
+    }
+    template <int MO, bool S, int D>
+    void go()
+    {
+        if constexpr (D == 3)
+            if (A.g.n[0] * A.g.n[1] * A.g.n[2] > 2 * kWgMaxThreads) return run<MO, S, D, true>();
+        run<MO, S, D, D == 1>();
     }
 };
 

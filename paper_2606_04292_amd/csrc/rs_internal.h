@@ -83,7 +83,7 @@ struct Step {
 };
 
 // 1-D levels of at most this many nodes run in the one-work-group cycle
-// (cycle_wg.h; 2-D and 3-D levels: wg_level_fits).
+// (cycle_wg.h; 2-D and 3-D levels: wg_cycle_level).
 constexpr long long kTailNodes = 2049;
 
 // ---------------------------------------------------------------------------
