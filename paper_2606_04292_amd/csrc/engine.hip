@@ -626,10 +626,12 @@ struct SlotMems {
 };
 
 // One work-group per request runs its small levels: those that fit the one-
-// work-group cycle (cycle_wg.h) in LDS, the ones above them (a 65^2 or 17^3
-// level under the default tail_nodes) from memory.  The largest requests of a
-// round set the launch's time: 372 us on memory-layout LDS arrays with every
-// node's record read anew in each pass, 128 requests of the stream.
+// work-group cycle (cycle_wg.h) in LDS, the ones above them from memory.  Under
+// the default tail_nodes those are a 65^2 or 17^3 level, and only of a request
+// that uses all of max_wide_levels above it (plan_request makes such a level a
+// wide one while a depth is left): 1025^2 with the default four.  The largest
+// requests of a round set the launch's time: 372 us on memory-layout LDS arrays
+// with every node's record read anew in each pass, 128 requests of the stream.
 __global__ __launch_bounds__(kWgMaxThreads) void e_tail(const EList *__restrict__ TL,
                                                         const ESlot *__restrict__ slots,
                                                         const EDyn *__restrict__ dyn,
