@@ -64,8 +64,8 @@ typedef struct rs_engine_opts {
                              a|theta|, xi|psi_i|, m_ij (|psi_i| + |psi_j|)); a stall
                              above that fails the request with RS_ENOTCONV */
     int rounds_per_tick;  /* correction rounds queued per rs_engine_tick, >= 1 */
-    int use_graph;        /* 1: replay a captured HIP graph per round (one per wide depth,
-                             captured when first used); 0: plain launches */
+    int use_graph;        /* 1: replay a captured HIP graph per round (one per number of
+                             wide depths, captured by rs_engine_create); 0: plain launches */
 } rs_engine_opts;
 
 typedef struct rs_request_stats {

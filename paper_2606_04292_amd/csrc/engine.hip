@@ -20,10 +20,12 @@
 //     transition (history update and next step's set-up) or failure.
 //
 // The sequence has a fixed launch shape (work-group counts do not depend on
-// which slots are resident), so it is captured once as a HIP graph and
-// replayed.  Each node's arithmetic is that of the single-grid kernels
-// (cell64.h, cell32.h, transfer.h) and depends only on its own slot's data, so
-// a request's result does not depend on the mix it runs in.
+// which slots are resident) for each number of wide depths, so it is captured as
+// one HIP graph per number when the engine is created, where a failure refuses
+// the engine, and replayed: a tick neither captures nor allocates.  Each node's
+// arithmetic is that of the single-grid kernels (cell64.h, cell32.h, transfer.h)
+// and depends only on its own slot's data, so a request's result does not depend
+// on the mix it runs in.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1126,6 +1128,8 @@ int rs_engine_create(const rs_engine_opts *o, void *arena_dev, size_t arena_byte
     }
     E->lists_dirty = true;
     e = upload_lists(E);
+    for (int d = 0; d <= o->max_wide_levels && e == RS_OK && o->use_graph; ++d)
+        e = capture_graph(E, d);
     if (e == RS_OK && hipStreamSynchronize(E->stream) != hipSuccess)
         e = fail(RS_EHIP, "engine set-up");
     if (e) {
@@ -1241,10 +1245,6 @@ int rs_engine_tick(rs_engine *E, int *done, int max_done, int *n_done, int *n_ac
     for (int s = 0; s < E->hi_slot; ++s)
         if (E->ticket[s] >= 0) depths = std::max(depths, E->plans[s].wide);
     if (depths >= 0) {
-        if (E->o.use_graph && !E->exec[depths]) {   // on first use of that depth
-            int e = capture_graph(E, depths);
-            if (e) return e;
-        }
         for (int r = 0; r < E->o.rounds_per_tick; ++r) {
             if (E->exec[depths]) HIPCALL(hipGraphLaunch(E->exec[depths], E->stream));
             else enqueue_round(E, depths);
