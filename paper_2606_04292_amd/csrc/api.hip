@@ -263,6 +263,7 @@ struct rs_grid {
     Law *soil_tab;                    // device table of per-soil laws (layered media)
     int tail_top;                     // first level of the one-work-group cycle (nlev: none)
     int tiles;                        // bit l: level l runs in tiles (route_levels)
+    int launched_sweeps;              // RS_SWEEP is set (route_levels)
     Law law;
     Law32 law32;
     bool law_set;
@@ -472,11 +473,11 @@ hipError_t prof_slot(rs_grid *G)
 // colour, takes 10.7 us there against 9.1 in two launches, two sweeps 15.1
 // against 19.4: such a level takes it from two sweeps on.  RS_SWEEP set keeps
 // levels of more than 1024 nodes with the sweep kernels.
-bool wg_sweep_level(const LevelData &f, int nsweeps)
+bool wg_sweep_level(const rs_grid *G, const LevelData &f, int nsweeps)
 {
     if (nsweeps <= 0 || !wg_level_fits(f.geo)) return false;
     if (f.geo.N > 2 * kWgMaxThreads && nsweeps < 2) return false;
-    return f.geo.N <= 1024 || !getenv("RS_SWEEP");
+    return f.geo.N <= 1024 || !G->launched_sweeps;
 }
 
 // nsweeps red-black sweeps on level l, counted, and timed on the finest level
@@ -498,7 +499,7 @@ int sweep_level(rs_grid *G, int l, int nsweeps)
         HIPCALL(hipEventRecord(G->prof_ev[2 * G->prof_used], G->stream));
     }
     int launches = 1;
-    if (wg_sweep_level(f, nsweeps)) {
+    if (wg_sweep_level(G, f, nsweeps)) {
         WgCycle<double> A{wg_geo(f.geo), 1, 0, 0, nsweeps, f.psi, f.g};
         WgMems<double> M;
         M.lv[0] = WgMem<double>{f.K, nullptr, f.beta, f.geo.soil, f.lambdaU};
@@ -672,15 +673,16 @@ double wg_updates(const rs_grid *G, int l, int nu1, int nu2);
 // launches.
 constexpr long long kTileMaxNodes = 1ll << 17;
 
-// Which levels do is decided once, at the entry of a call that runs cycles: the
-// parts of one cycle have to agree (a tiled way down leaves the smoothed iterate
-// in the level's second array and the coarse level ready, a plain one its defect
-// there), also where a part is captured into a graph with the profiling events
-// off or the environment changes meanwhile.
+// Which levels do is decided once, at the entry of a call that sweeps: the parts
+// of one cycle have to agree (a tiled way down leaves the smoothed iterate in the
+// level's second array and the coarse level ready, a plain one its defect there),
+// also where a part is captured into a graph with the profiling events off or the
+// environment changes meanwhile.
 void route_levels(rs_grid *G)
 {
     G->tiles = 0;
-    if (getenv("RS_SWEEP")) return;
+    G->launched_sweeps = getenv("RS_SWEEP") ? 1 : 0;
+    if (G->launched_sweeps) return;
     for (int l = G->prof_on ? 1 : 0; l < G->tail_top && l < G->nlev - 1; ++l) {
         const Geo &g = G->lev[l].geo;
         // the smallest halo of a sweep and of a transfer with one sweep fit
@@ -878,7 +880,7 @@ int fine_up(rs_grid *G, int which, int nu2)
 struct CycleKey {
     double a, dt;
     int order, lag_extrap, nu1, nu2, nu_coarse, law_version;
-    int tiles;   // bit l: level l runs in tiles
+    int tiles, launched_sweeps;   // as in rs_grid
     double lambdaU[kMaxLevels];
 };
 
@@ -905,6 +907,7 @@ int coarse_cycle(rs_grid *G, int which, int nu1, int nu2)
     k.law_version = G->law_version;
     for (int l = 0; l < G->nlev; ++l) k.lambdaU[l] = G->lev[l].lambdaU;
     k.tiles = G->tiles;
+    k.launched_sweeps = G->launched_sweeps;
     if (!G->cg[which] || memcmp(&k, G->cg_key[which], sizeof k) != 0) {
         if (G->cg[which]) {
             HIPCALL(hipStreamSynchronize(G->stream));   // a replay may still run
@@ -1409,6 +1412,7 @@ int rs_sweep(rs_grid *G, int level, int nsweeps)
     if (!G->in_step) return fail(RS_ESTATE, "no active step (call rs_begin_step)");
     if (level < 0 || level >= G->nlev) return fail(RS_EINVAL, "level out of range");
     if (nsweeps < 0) return fail(RS_EINVAL, "nsweeps < 0");
+    route_levels(G);
     int e = sweep_level(G, level, nsweeps);
     if (e) return e;
     HIPCALL(hipGetLastError());
