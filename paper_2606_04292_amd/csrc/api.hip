@@ -4,6 +4,7 @@
 // in the kernels; the host only sequences launches and reads back norms.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1572,9 +1573,12 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
             WgCycle<double> A;
             WgMems<double> M;
             wg_args(G, 0, o->nu1, o->nu2, &A, &M);
-            const int left = o->max_cycles - cycles;
-            const WgSolve S{o->tol_abs, best, slow, o->stagnation,
-                            left < kWgSolveCycles ? left : kWgSolveCycles, first_norm ? 1 : 0};
+            const double sweeps = (double)(G->nlev - 1) * ((double)o->nu1 + (double)o->nu2) +
+                                  (double)o->nu_coarse;
+            int most = std::min(o->max_cycles - cycles, kWgSolveCycles);
+            if (most * sweeps > kWgSolveSweeps)
+                most = std::max(1, (int)(kWgSolveSweeps / sweeps));
+            const WgSolve S{o->tol_abs, best, slow, o->stagnation, most, first_norm ? 1 : 0};
             launch_solve_wg(A, M, G->law, G->step.a, G->desc.dim, S,
                             (WgSolveOut *)(G->host_dev + kScratchWords), G->stream);
             HIPCALL(hipGetLastError());

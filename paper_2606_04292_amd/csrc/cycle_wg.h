@@ -36,8 +36,11 @@
 namespace rs {
 
 constexpr int kWgMaxLev = 12;        // levels of one cycle (2049 nodes on the shortest axis)
-// Cycles of one launch of the whole-grid solve (a few milliseconds at most).
+// Cycles of one launch of the whole-grid solve at most, and sweeps (on all levels;
+// one cycle at least): a sweep takes 2 to 5 us with three Newton steps, so a launch
+// some 40 ms at most unless one cycle alone is longer.
 constexpr int kWgSolveCycles = 60;
+constexpr int kWgSolveSweeps = 8192;
 // Three waves per SIMD, so a lane may hold 168 registers (2-D and most 3-D levels
 // take one node per thread and colour; with two the 3-D kernels spill).
 constexpr int kWgMaxThreads = 768;

@@ -74,3 +74,28 @@ def test_the_cycles_of_a_step_are_those_of_vcycle_calls(name, cycles):
         G.vcycle()
     _same("%s, %d cycles" % (name, done), x, np_(G.psi()))
     G.close()
+
+
+@pytest.mark.parametrize("name", ["1d_127_slots", "1d_1025_sink", "2d_33x33", "3d_5x5x5", "soils_33"])
+def test_the_stopping_test_crosses_launches(name):
+    """So many sweeps on the coarsest level are allowed that a launch of the whole-grid solve
+    holds two cycles: the step ends where the stopping rule ends V-cycle calls."""
+    w = CASES[name]
+    G = rsl.Grid(w)
+    code, st = G.bdf_step(opts=rsl.solve_opts(w.nu1, w.nu2, 3000, max_cycles=100, tol_abs=0.0,
+                                              stagnation=1))
+    assert code == rsl.RS_OK, rsl.lib().rs_last_error()
+    x = np_(G.get_state()[0])
+    # the same cycles one by one (the coarsest level's sweeps stay as set by the step)
+    G.set_state(torch.as_tensor(w.psi0))
+    G.begin_step()
+    best, slow, hist = G.residual_norm(), 0, []
+    while slow < 2:
+        hist.append(G.vcycle(want_norm=True))
+        if hist[-1] == 0.0:
+            break
+        best, slow = (hist[-1], 0) if hist[-1] < best else (best, slow + 1)
+    say("launches", name, "cycles", st.cycles, len(hist))
+    assert st.cycles == len(hist) and list(st.res_hist[1:1 + len(hist)]) == hist[:63]
+    _same(name, x, np_(G.psi()))
+    G.close()
