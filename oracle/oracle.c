@@ -74,7 +74,7 @@
 #define ORC_FIELD_PSI_N 4
 #define ORC_FIELD_PSI_NM1 5
 
-#define ORC_MAXLEV 16
+#define ORC_MAXLEV 30
 
 typedef struct {
     int dim;

@@ -157,6 +157,7 @@ struct Layout {
 };
 
 constexpr int kScratchWords = 64;
+static_assert(1 + kMaxLevels < kScratchWords, "norm word, one word per level, scale word");
 // Pinned host words: the scratch words' mirror, then a whole-grid solve's report.
 constexpr int kHostWords = kScratchWords + (int)((sizeof(WgSolveOut) + 7) / 8);
 

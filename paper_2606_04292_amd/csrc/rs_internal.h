@@ -7,7 +7,8 @@
 
 namespace rs {
 
-constexpr int kMaxLevels = 16;
+// Levels of the largest grid: fewer than 2^31 nodes, so an axis of at most 2^30 + 1.
+constexpr int kMaxLevels = 30;
 constexpr int kBcDirichlet = 1;
 constexpr int kBcNoflux = 2;
 constexpr int kBcFreedrain = 3;
