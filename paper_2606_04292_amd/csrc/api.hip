@@ -261,7 +261,6 @@ struct rs_grid {
     unsigned long long *scratch;
     unsigned long long *host_bits;   // readback words
     unsigned long long *host_dev;    // their device address (pinned; null on static grids)
-    hipEvent_t norm_ev;               // a norm has reached host_bits (with host_dev)
     Law *soil_tab;                    // device table of per-soil laws (layered media)
     int tail_top;                     // first level of the one-work-group cycle (nlev: none)
     int tiles;                        // bit l: level l runs in tiles (route_levels)
@@ -520,28 +519,18 @@ int sweep_level(rs_grid *G, int l, int nsweeps)
     return RS_OK;
 }
 
-// The norm word's way to the host: queued behind the kernel that formed it
-// (norm_send), read once it has arrived (norm_wait; what was queued in between
-// keeps running).  The word is zero again for the next norm.
-int norm_send(rs_grid *G)
+// The norm behind the kernel that formed it; its word is zero again for the next.
+int read_norm(rs_grid *G, double *out)
 {
     if (G->host_dev) {
         launch_norm_out(G->scratch, G->host_dev, G->stream);
-        HIPCALL(hipGetLastError());
-        HIPCALL(hipEventRecord(G->norm_ev, G->stream));
-        return RS_OK;
+    } else {
+        HIPCALL(hipMemcpyAsync(G->host_bits, G->scratch, sizeof(unsigned long long),
+                               hipMemcpyDeviceToHost, G->stream));
+        launch_fill_u64(G->scratch, 1, 0ull, G->stream);
     }
-    HIPCALL(hipMemcpyAsync(G->host_bits, G->scratch, sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, G->stream));
-    launch_fill_u64(G->scratch, 1, 0ull, G->stream);
     HIPCALL(hipGetLastError());
-    return RS_OK;
-}
-
-int norm_wait(rs_grid *G, double *out)
-{
-    if (G->host_dev) HIPCALL(hipEventSynchronize(G->norm_ev));
-    else HIPCALL(hipStreamSynchronize(G->stream));
+    HIPCALL(hipStreamSynchronize(G->stream));
     if (G->prof_used) {
         int e = harvest_profile(G);
         if (e) return e;
@@ -551,22 +540,16 @@ int norm_wait(rs_grid *G, double *out)
     return RS_OK;
 }
 
-// FP64 defect max-norm of the finest level, on its way to the host (and the
-// defect vector into d; or, with mp_start, the start of an FP32 correction:
-// rhs = fl32(defect), psi_b = fl32(psi), delta = 0).
-int fine_norm_send(rs_grid *G, double *d = nullptr, bool mp_start = false)
+// FP64 defect max-norm of the finest level (and the defect vector into d; or,
+// with mp_start, the start of an FP32 correction: rhs = fl32(defect),
+// psi_b = fl32(psi), delta = 0).
+int fine_norm(rs_grid *G, double *out, double *d = nullptr, bool mp_start = false)
 {
     LevelData &f = G->lev[0];
     MpStart mp{};
     if (mp_start) mp = MpStart{f.rhs32, f.pb32, f.dl};
     launch_residual(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, d, G->scratch, G->stream, mp);
-    return norm_send(G);
-}
-
-int fine_norm(rs_grid *G, double *out, double *d = nullptr, bool mp_start = false)
-{
-    int e = fine_norm_send(G, d, mp_start);
-    return e ? e : norm_wait(G, out);
+    return read_norm(G, out);
 }
 
 bool tile_level(const rs_grid *G, int l);
@@ -574,21 +557,20 @@ template <typename T>
 void tile_phase(rs_grid *G, int l, int phase, int nu, unsigned long long *norm);
 
 // The pre-smoothing of an FP64 cycle on the finest level and the max-norm of
-// the defect it leaves, on its way to the host (the defect vector into d): where the level runs the
-// pair sweep, the last colour pass forms the defect of its nodes on the way
+// the defect it leaves (the defect vector into d): where the level runs the pair sweep, the last colour pass forms the defect of its nodes on the way
 // and one more pass that of the others; otherwise the sweeps, then the defect
 // kernel.  The same d and norm either way.  A tiled level leaves the smoothed
 // iterate in d instead, and its coarse level ready.
-int presmooth_send(rs_grid *G, int nu1)
+int presmooth_norm(rs_grid *G, int nu1, double *out)
 {
     LevelData &f = G->lev[0];
     if (tile_level(G, 0)) {
         tile_phase<double>(G, 0, kTileDown, nu1, G->scratch);
-        return norm_send(G);
+        return read_norm(G, out);
     }
     if (f.psi_alt || !sweep_defect_level(f.geo, G->law, nu1)) {
         int e = sweep_level(G, 0, nu1);
-        return e ? e : fine_norm_send(G, f.d);
+        return e ? e : fine_norm(G, out, f.d);
     }
     // the plain colour passes are timed like any sweep batch of the level
     const bool timed = G->prof_on;
@@ -607,7 +589,7 @@ int presmooth_send(rs_grid *G, int nu1)
     launch_sweep_defect(f.geo, G->law, G->step, f.beta, f.K, f.g, f.psi, nu1, f.d, G->scratch, 1,
                         G->stream);
     G->updates += (double)nu1 * (double)f.unknowns;
-    return norm_send(G);
+    return read_norm(G, out);
 }
 
 // Scale of the defect's rounding floor on the finest level: the largest sum
@@ -950,15 +932,6 @@ int coarse_cycle(rs_grid *G, int which, int nu1, int nu2)
     return RS_OK;
 }
 
-// The FP32 correction cycle from the finest level down to its coarse part's end
-// (grids above the one-work-group cycle).
-void fine_down32(rs_grid *G, int nu1, int nu2)
-{
-    if (tile_level(G, 0)) tile_phase<float>(G, 0, kTileDown, nu1, nullptr);
-    else sweep32_level(G, 0, nu1);
-    (void)coarse_cycle(G, 1, nu1, nu2);
-}
-
 // FP32 FAS V-cycle on the correction equation (same structure as the FP64 one).
 void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
 {
@@ -980,7 +953,9 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
         return;
     }
     if (l == 0) {
-        fine_down32(G, nu1, nu2);
+        if (tile_level(G, 0)) tile_phase<float>(G, 0, kTileDown, nu1, nullptr);
+        else sweep32_level(G, 0, nu1);
+        (void)coarse_cycle(G, 1, nu1, nu2);
         (void)fine_up(G, 1, nu2);
         return;
     }
@@ -1004,10 +979,9 @@ void vcycle32_level(rs_grid *G, int l, int nu1, int nu2)
 // right-hand side fl32(r), the base state fl32(psi) and delta = 0 on the finest
 // level (fine_norm with mp_start); psi_b is injected into the coarse levels
 // once, FP32 cycles solve the correction equation and psi += delta in FP64.
-// The head (injection, the first cycle down to the end of its coarse part)
-// touches FP32 arrays only.
-void mp_head(rs_grid *G, int nu1, int nu2)
+void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
 {
+    LevelData &f = G->lev[0];
     Geo geo[kMaxLevels];
     float *pb[kMaxLevels];
     for (int l = 0; l < G->nlev; ++l) {
@@ -1015,22 +989,8 @@ void mp_head(rs_grid *G, int nu1, int nu2)
         pb[l] = G->lev[l].pb32;
     }
     launch_inject_base32(geo, pb, G->nlev, G->stream);
-    if (G->tail_top > 0 && G->nlev > 1) fine_down32(G, nu1, nu2);
-    else vcycle32_level(G, 0, nu1, nu2);
-}
-
-void mp_tail(rs_grid *G, int inner, int nu1, int nu2)
-{
-    LevelData &f = G->lev[0];
-    if (G->tail_top > 0 && G->nlev > 1) (void)fine_up(G, 1, nu2);
-    for (int c = 1; c < inner; ++c) vcycle32_level(G, 0, nu1, nu2);
+    for (int c = 0; c < inner; ++c) vcycle32_level(G, 0, nu1, nu2);
     launch_apply_delta(f.geo.N, f.dl, f.psi, G->stream);
-}
-
-void mp_correction(rs_grid *G, int inner, int nu1, int nu2)
-{
-    mp_head(G, nu1, nu2);
-    mp_tail(G, inner, nu1, nu2);
 }
 
 // The FP64 one-work-group cycle from level l down.
@@ -1242,8 +1202,7 @@ int rs_create_grid(const rs_grid_desc *d, int precision, void *ws_dev, size_t ws
     }
     grid_view(G, d, precision, L, (char *)ws_dev, (hipStream_t)stream, bits);
     void *dev = nullptr;
-    if (hipHostGetDevicePointer(&dev, bits, 0) == hipSuccess && dev &&
-        hipEventCreateWithFlags(&G->norm_ev, hipEventDisableTiming) == hipSuccess)
+    if (hipHostGetDevicePointer(&dev, bits, 0) == hipSuccess && dev)
         G->host_dev = (unsigned long long *)dev;
     else
         (void)hipGetLastError();   // norms by copy
@@ -1265,7 +1224,6 @@ void rs_destroy_grid(rs_grid *G)
         if (G->cg[w]) (void)hipGraphExecDestroy(G->cg[w]);
     if (G->cap) (void)hipStreamDestroy(G->cap);
     for (hipEvent_t ev : G->prof_ev) (void)hipEventDestroy(ev);
-    if (G->host_dev) (void)hipEventDestroy(G->norm_ev);
     if (G->host_bits) (void)hipHostFree(G->host_bits);
     delete G;
 }
@@ -1499,10 +1457,6 @@ int rs_end_step(rs_grid *G)
     return RS_OK;
 }
 
-namespace {
-constexpr long long kAheadNodes = 1ll << 20;
-}
-
 int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_step_stats *st)
 {
     if (!G || !o) return fail(RS_EINVAL, "null argument");
@@ -1516,26 +1470,6 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     if (e) return e;
     const bool mixed = G->precision == RS_MIXED;
     const int inner = o->mp_inner_cycles > 0 ? o->mp_inner_cycles : 1;
-    // Grids of at most kAheadNodes nodes queue the next cycle's coarse part (it
-    // leaves the fine iterate alone) before they wait for the norm that decides
-    // whether the cycle is run, so that the device does not idle while the host
-    // reads the norm and launches.  The one queued in vain at a step's end costs
-    // what a cycle's coarse part takes, which the gaps of the step's cycles
-    // outweigh on small grids (15 to 25 us each).
-    // Not while profiling (its events would still be running), nor where the
-    // norm comes by a copy that waits for the whole stream.
-    const bool ahead = G->lev[0].geo.N <= kAheadNodes && G->host_dev && !G->prof_on;
-    bool first = true;           // no cycle of the step has run
-    bool queued = false;         // the next correction's head / cycle's coarse part
-    double queued_updates = 0.0; // its pointwise updates, counted once it is used
-    auto queue_head = [&](bool want) {
-        queued = ahead && want && !(o->fmg && first);
-        if (!queued) return;
-        const double u = G->updates;
-        mp_head(G, o->nu1, o->nu2);
-        queued_updates = G->updates - u;
-        G->updates = u;
-    };
     // FP64 grids that fit one work-group run their cycles and the stopping test
     // in it, kWgSolveCycles to a launch.
     const bool whole = !mixed && G->nlev > 1 && G->tail_top == 0 && G->host_dev &&
@@ -1547,10 +1481,7 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
     G->updates = 0.0;
     const bool first_in_solve = whole && !o->fmg;
     if (!first_in_solve) {
-        e = fine_norm_send(G, nullptr, mixed);   // mixed: with the first correction's start
-        if (e) return e;
-        if (mixed) queue_head(o->max_cycles > 0);
-        e = norm_wait(G, &r);
+        e = fine_norm(G, &r, nullptr, mixed);   // mixed: with the first correction's start
         if (e) return e;
         r0 = r;
         best = r;
@@ -1604,17 +1535,7 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
         if (test_in_cycle && !(o->fmg && cycles == 0)) {
             double rn;
             in_d = tile_level(G, 0);
-            e = presmooth_send(G, o->nu1);
-            if (e) return e;
-            const double u = G->updates;
-            const bool early = ahead && cycles + 1 < o->max_cycles;
-            if (early) {
-                e = coarse_cycle(G, 0, o->nu1, o->nu2);
-                if (e) return e;
-                queued_updates = G->updates - u;
-                G->updates = u;
-            }
-            e = norm_wait(G, &rn);
+            e = presmooth_norm(G, o->nu1, &rn);
             if (e) return e;
             ++cycles;
             if (nh < 64) hist[nh++] = rn;
@@ -1630,8 +1551,7 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
             }
             fresh = false;
             if (!(std::isfinite(rn) && rn > o->tol_abs) || cycles >= o->max_cycles) break;
-            if (early) G->updates += queued_updates;
-            else e = coarse_cycle(G, 0, o->nu1, o->nu2);
+            e = coarse_cycle(G, 0, o->nu1, o->nu2);
             if (!e) e = fine_up(G, 0, o->nu2);
             if (e) return e;
             in_d = false;
@@ -1643,20 +1563,14 @@ int rs_bdf_step(rs_grid *G, double dt, int order, const rs_solve_opts *o, rs_ste
             e = fmg_cycle(G, o->nu1, o->nu2);
             if (e) return e;
         } else if (mixed) {
-            if (queued) G->updates += queued_updates;
-            else mp_head(G, o->nu1, o->nu2);
-            mp_tail(G, inner, o->nu1, o->nu2);
+            mp_correction(G, inner, o->nu1, o->nu2);
         } else {
             e = vcycle_level(G, 0, o->nu1, o->nu2);
             if (e) return e;
         }
-        first = false;
         HIPCALL(hipGetLastError());
         double rn;
-        e = fine_norm_send(G, nullptr, mixed);
-        if (e) return e;
-        if (mixed) queue_head(cycles + 1 < o->max_cycles);
-        e = norm_wait(G, &rn);
+        e = fine_norm(G, &rn, nullptr, mixed);
         if (e) return e;
         ++cycles;
         if (nh < 64) hist[nh++] = rn;
