@@ -650,9 +650,12 @@ double wg_updates(const rs_grid *G, int l, int nu1, int nu2);
 
 // Levels that run in tiles: 1-D and 2-D levels above the one-work-group cycle
 // of at most kTileMaxNodes nodes.  A V(2,2) visit of a vGM level, plain
-// launches against tiles (us of kernel time): 129^2 53 against 29, 257^2 55
+// launches against tiles (us of kernel time): 129^2 53 against 27, 257^2 55
 // against 30, but 513^2 66 against 91, where the 4.3 loads of the halo make
-// the tiles' arithmetic the longer way.  RS_SWEEP (any sweep kernel picked by
+// the tiles' arithmetic the longer way (a V(2,2) cycle of 513^2 209 plain, 225
+// in tiles).  There are few sizes between: 257x513 and its like (131 841 to
+// 135 201 nodes) take 4 to 12 % less in tiles, which this line leaves out.
+// RS_SWEEP (any sweep kernel picked by
 // hand) and profiling of the finest level's colour passes keep the plain
 // launches.
 constexpr long long kTileMaxNodes = 1ll << 17;
@@ -679,7 +682,7 @@ void route_levels(rs_grid *G)
 bool tile_level(const rs_grid *G, int l) { return (G->tiles >> l) & 1; }
 
 // One launch of a tiled phase with ns sweeps: its halo, tiles, and an estimate
-// of its time in us (12 to 15 measured for a launch with four colour passes on
+// of its time in us (12 to 17 measured for a launch with four colour passes on
 // up to 512 tiles, the two work-groups per CU that are resident; a launch of
 // which 3 are dispatch, arguments and the loads, a pass and the transfer about
 // 1.5 each for the vGM law).

@@ -13,7 +13,8 @@
 //    right-hand side and own value in registers: a colour pass reads 2 DIM
 //    neighbour values, solves and writes one value.  Power terms of the law are
 //    not carried from solve to solve: scaled on from one to the next, their
-//    roundings add up (5.8 half-ulps of psi rms after ten visits against 2.8);
+//    roundings would add up over a solve's history, and a sweep's result would
+//    depend on it (they save 12 % of a 257-node column's step);
 //  - nodes of one colour are the even (odd) positions of the lexicographic
 //    order (all axes have an odd node count), so slots map to nodes without
 //    padding; levels of at most 64 nodes per colour run on one wave without
@@ -23,9 +24,9 @@
 // takes 76 cycles and an LDS round trip about 70, so a colour pass of 1000
 // cycles is the instruction count of its solve.  Steps against the same cycle
 // on generic pointers with every coefficient formed anew in each pass: 257-node
-// vGM column (three Newton steps per solve) 3.29 -> 2.32 ms for two steps,
-// 2049-node Haverkamp column V(5,5) 7.9 -> 4.55 ms for three, 65^3 block (its
-// 9^3 level and below) 8.8 -> 7.5 ms for two.
+// vGM column (three Newton steps per solve) 3.39 -> 2.36 ms for two steps,
+// 2049-node Haverkamp column V(5,5) 7.8 -> 4.8 ms for three, 65^3 block (its
+// 9^3 level and below) 8.75 -> 7.35 ms for two.
 #pragma once
 
 #include "rs_internal.h"

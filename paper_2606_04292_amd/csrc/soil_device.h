@@ -311,9 +311,9 @@ __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double 
     double x = x0;
     bool done = false;
     PowState ps = pow_none();
-    // three copies of the iteration pay for the Haverkamp law (257^3 sweep 89.8 ->
-    // 88.1 us); of the longer vGM law with a sink they spill scalar registers
-    // (root box, a step: 13.3 -> 14.1 ms)
+    // three copies of the iteration pay for the Haverkamp law (257^3 block, a step
+    // 32.9 -> 32.5 ms); of the longer vGM law they do not (root box 14.05 -> 14.3,
+    // 513^2 slice 7.55 -> 7.88: with a sink they spill scalar registers)
     const int iters = NEWTON > 0 ? NEWTON : L.newton;
 #pragma clang loop unroll_count(NEWTON == 3 && MODEL == kHaverkamp ? 3 : 1)
     for (int k = 0; k < iters; ++k) {
