@@ -470,14 +470,15 @@ hipError_t prof_slot(rs_grid *G)
 }
 
 // Levels whose sweeps run in one work-group, all in one launch (k_sweeps_wg):
-// what fits it.  One sweep of a 2049-node column, two nodes per thread and
-// colour, takes 10.7 us there against 9.1 in two launches, two sweeps 15.1
-// against 19.4: such a level takes it from two sweeps on.  RS_SWEEP set keeps
-// levels of more than 1024 nodes with the sweep kernels.
+// what fits it.  On a 2049-node column, two nodes per thread and colour, two
+// sweeps take 14 (values at rest) to 21 us (three Newton steps per solve) there
+// and 15.5 in launches per colour, three 19 to 29 against 24: such a level takes it
+// from three sweeps on.  RS_SWEEP set keeps levels of more than 1024 nodes with
+// the sweep kernels.
 bool wg_sweep_level(const rs_grid *G, const LevelData &f, int nsweeps)
 {
     if (nsweeps <= 0 || !wg_level_fits(f.geo)) return false;
-    if (f.geo.N > 2 * kWgMaxThreads && nsweeps < 2) return false;
+    if (f.geo.N > 2 * kWgMaxThreads && nsweeps < 3) return false;
     return f.geo.N <= 1024 || !G->launched_sweeps;
 }
 

@@ -52,9 +52,11 @@ __global__ __launch_bounds__(kWgMaxThreads) void k_solve_wg(WgCycle<double> A, W
 // A.nuc sweeps of one level: the visit of the cycle's coarsest one, with no sweep
 // left out.  Bound by the chain of barriers and solves of one work-group, so the
 // level is loaded once and its nodes and face coefficients stay in registers.
-// Against one launch per colour, two and twenty sweeps: 1025 nodes 19.2 -> 9.9 and
-// 169 -> 61 us, 33^2 21.2 -> 11.6 and 181 -> 71, 9x9x17 21.3 -> 12.8 and 181 -> 73
-// (vGM).
+// Against one launch per colour, two and twenty sweeps: 1025 nodes 19.2 -> 9.4 and
+// 169 -> 60 us, 33^2 21.2 -> 11.0 and 181 -> 70, 9x9x17 21.3 -> 12.2 and 181 -> 72
+// (vGM).  Against a work-group on global memory, which suits a single sweep of a
+// few hundred nodes: 9x9x3 nodes, one sweep 6.0 -> 6.7, two 9.6 -> 8.4, six 24.4 ->
+// 16.4.
 template <int MODEL, bool SINK, int DIM>
 __global__ __launch_bounds__(kWgMaxThreads) void k_sweeps_wg(WgCycle<double> A, WgMems<double> M,
                                                              Law L, double a)

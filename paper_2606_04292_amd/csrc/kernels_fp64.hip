@@ -186,17 +186,17 @@ __device__ __forceinline__ PointEq ngs_reduce(const Geo &g, const Law &L, const 
 }
 
 // The safeguarded Newton solve of a reduced point problem.
-template <int MODEL, bool SINK>
+template <int MODEL, bool SINK, int DIM>
 __device__ __forceinline__ double ngs_solve(const Geo &g, const Law &L, double a, const PointEq &e,
                                             double x0, long long idx)
 {
     if constexpr (MODEL == kMulti) {
         const Law &Ls = L.soils[g.soil[idx]];
-        return (L.newton == 3) ? local_solve_soil<SINK, 3>(Ls, a, e.b, e.cc, e.f, x0)
-                               : local_solve_soil<SINK, 0>(Ls, a, e.b, e.cc, e.f, x0);
+        return (L.newton == 3) ? local_solve_soil<SINK, 3, DIM>(Ls, a, e.b, e.cc, e.f, x0)
+                               : local_solve_soil<SINK, 0, DIM>(Ls, a, e.b, e.cc, e.f, x0);
     } else {
-        return (L.newton == 3) ? local_solve_t<MODEL, SINK, 3>(L, a, e.b, e.cc, e.f, x0)
-                               : local_solve_t<MODEL, SINK, 0>(L, a, e.b, e.cc, e.f, x0);
+        return (L.newton == 3) ? local_solve_t<MODEL, SINK, 3, DIM>(L, a, e.b, e.cc, e.f, x0)
+                               : local_solve_t<MODEL, SINK, 0, DIM>(L, a, e.b, e.cc, e.f, x0);
     }
 }
 
@@ -209,7 +209,7 @@ __device__ __forceinline__ double ngs_point(const Geo &g, const Law &L, double a
 {
     const PointEq e = ngs_reduce<SINK, DIM>(g, L, beta, lambdaU, st, Ki, Kn, pn, f, x0, i, j, k,
                                             colour);
-    return ngs_solve<MODEL, SINK>(g, L, a, e, x0, idx);
+    return ngs_solve<MODEL, SINK, DIM>(g, L, a, e, x0, idx);
 }
 
 // Defect g_i - N_i(psi) of unknown i (column i of its row) at idx from its
@@ -553,13 +553,13 @@ __global__ __launch_bounds__(256) void k_sweep_pair(Geo g, Law L, Step st, const
         e[a] = ngs_reduce<SINK, DIM, false>(g, L, beta, lambdaU, sn, a ? KK.y : KK.x, Kn, pn,
                                      a ? G2.y : G2.x, a ? P.y : P.x, i, (int)j, (int)k, colour);
     }
-    const double xa = dir_a ? P.x : ngs_solve<MODEL, SINK>(g, L, st.a, e[0], P.x, idx);
+    const double xa = dir_a ? P.x : ngs_solve<MODEL, SINK, DIM>(g, L, st.a, e[0], P.x, idx);
     __builtin_amdgcn_sched_barrier(0);
     if (!has_b) {
         buf_st(rP, vo, xa);
         return;
     }
-    const double xb = dir_b ? P.y : ngs_solve<MODEL, SINK>(g, L, st.a, e[1], P.y, idx + 1);
+    const double xb = dir_b ? P.y : ngs_solve<MODEL, SINK, DIM>(g, L, st.a, e[1], P.y, idx + 1);
     buf_st2(rP, vo, xa, xb);
 }
 
@@ -643,9 +643,9 @@ __global__ __launch_bounds__(256) void k_sweep_pair_defect(Geo g, Law L, Step st
                                                     a ? G2.y : G2.x, a ? P.y : P.x, i, (int)j,
                                                     (int)k, colour);
             }
-            if (!dir_a) xnew[0] = ngs_solve<MODEL, SINK>(g, L, st.a, e[0], P.x, idx);
+            if (!dir_a) xnew[0] = ngs_solve<MODEL, SINK, DIM>(g, L, st.a, e[0], P.x, idx);
             __builtin_amdgcn_sched_barrier(0);
-            if (!dir_b) xnew[1] = ngs_solve<MODEL, SINK>(g, L, st.a, e[1], P.y, idx + 1);
+            if (!dir_b) xnew[1] = ngs_solve<MODEL, SINK, DIM>(g, L, st.a, e[1], P.y, idx + 1);
             if (has_b) buf_st2(rP, vo, xnew[0], xnew[1]);
             else buf_st(rP, vo, xnew[0]);
         }
@@ -901,9 +901,9 @@ __global__ __launch_bounds__(256) void k_sweep_zm(Geo g, Law L, Step st, const d
                 }
                 const long long idx =
                     (long long)j * s1 + (long long)z * s2 + (par ? xh : 0) + p0 + 2 * q;
-                const double xa = dir_a ? P.x : ngs_solve<MODEL, SINK>(g, L, st.a, e[0], P.x, idx);
+                const double xa = dir_a ? P.x : ngs_solve<MODEL, SINK, 3>(g, L, st.a, e[0], P.x, idx);
                 const double xb =
-                    dir_b ? P.y : ngs_solve<MODEL, SINK>(g, L, st.a, e[1], P.y, idx + 1);
+                    dir_b ? P.y : ngs_solve<MODEL, SINK, 3>(g, L, st.a, e[1], P.y, idx + 1);
                 buf_st2(rP, (int)(idx * 8), xa, xb);
             }
         }

@@ -293,7 +293,7 @@ __device__ __forceinline__ void feddes(const Law &L, double x, double &a, double
 // terms, a (theta_r + ...): a product of a and the law's scale rounded once for the
 // whole grid (one instruction less) moved the fixed point of every node one way,
 // by up to 2 half-ulps of psi.
-template <int MODEL, bool SINK, int NEWTON>
+template <int MODEL, bool SINK, int NEWTON, int DIM = 0>
 __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double beta, double c,
                                                  double ic, double f, double x0)
 {
@@ -312,10 +312,12 @@ __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double 
     bool done = false;
     PowState ps = pow_none();
     // three copies of the iteration pay for the Haverkamp law (257^3 block, a step
-    // 32.9 -> 32.5 ms); of the longer vGM law they do not (root box 14.05 -> 14.3,
-    // 513^2 slice 7.55 -> 7.88: with a sink they spill scalar registers)
+    // 32.9 -> 32.5 ms) and on 1-D levels, where a colour pass is one solve's latency
+    // (4097 nodes 4.4 -> 4.0 us); of the longer vGM law on other levels they do not
+    // (root box 14.05 -> 14.3 ms, 513^2 slice 7.55 -> 7.88: with a sink they spill
+    // scalar registers)
     const int iters = NEWTON > 0 ? NEWTON : L.newton;
-#pragma clang loop unroll_count(NEWTON == 3 && MODEL == kHaverkamp ? 3 : 1)
+#pragma clang loop unroll_count(NEWTON == 3 && (MODEL == kHaverkamp || DIM == 1) ? 3 : 1)
     for (int k = 0; k < iters; ++k) {
         const ThetaEval t = theta_next<MODEL>(L, x, ps);
         double F = fma(c, x, a * t.th) - f;
@@ -344,33 +346,33 @@ __device__ __forceinline__ double local_solve_ic(const Law &L, double a, double 
     return x;
 }
 
-template <int MODEL, bool SINK, int NEWTON>
+template <int MODEL, bool SINK, int NEWTON, int DIM>
 __device__ __forceinline__ double local_solve_t(const Law &L, double a, double beta, double c,
                                                 double f, double x0)
 {
-    return local_solve_ic<MODEL, SINK, NEWTON>(L, a, beta, c, MODEL == kLinear ? 0.0 : rcp_nr(c),
+    return local_solve_ic<MODEL, SINK, NEWTON, DIM>(L, a, beta, c, MODEL == kLinear ? 0.0 : rcp_nr(c),
                                                f, x0);
 }
 
 // The pointwise solve with the law of one soil picked at run time (layered
 // media): the same iteration as local_solve_t for that soil's model.
-template <bool SINK, int NEWTON>
+template <bool SINK, int NEWTON, int DIM = 0>
 __device__ __forceinline__ double local_solve_soil_ic(const Law &Ls, double a, double beta,
                                                       double c, double ic, double f, double x0)
 {
     switch (Ls.model) {
-    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
-    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
-    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
-    default: return local_solve_ic<kLinear, SINK, NEWTON>(Ls, a, beta, c, ic, f, x0);
+    case kGardner: return local_solve_ic<kGardner, SINK, NEWTON, DIM>(Ls, a, beta, c, ic, f, x0);
+    case kHaverkamp: return local_solve_ic<kHaverkamp, SINK, NEWTON, DIM>(Ls, a, beta, c, ic, f, x0);
+    case kVgm: return local_solve_ic<kVgm, SINK, NEWTON, DIM>(Ls, a, beta, c, ic, f, x0);
+    default: return local_solve_ic<kLinear, SINK, NEWTON, DIM>(Ls, a, beta, c, ic, f, x0);
     }
 }
 
-template <bool SINK, int NEWTON>
+template <bool SINK, int NEWTON, int DIM = 0>
 __device__ __forceinline__ double local_solve_soil(const Law &Ls, double a, double beta, double c,
                                                    double f, double x0)
 {
-    return local_solve_soil_ic<SINK, NEWTON>(Ls, a, beta, c, rcp_nr(c), f, x0);
+    return local_solve_soil_ic<SINK, NEWTON, DIM>(Ls, a, beta, c, rcp_nr(c), f, x0);
 }
 
 // Node kinds from indices (no node-type array): Dirichlet if on a Dirichlet
