@@ -558,10 +558,11 @@ template <typename T>
 void tile_phase(rs_grid *G, int l, int phase, int nu, unsigned long long *norm);
 
 // The pre-smoothing of an FP64 cycle on the finest level and the max-norm of
-// the defect it leaves (the defect vector into d): where the level runs the pair sweep, the last colour pass forms the defect of its nodes on the way
-// and one more pass that of the others; otherwise the sweeps, then the defect
-// kernel.  The same d and norm either way.  A tiled level leaves the smoothed
-// iterate in d instead, and its coarse level ready.
+// the defect it leaves (the defect vector into d): where the level runs the pair
+// sweep, the last colour pass forms the defect of its nodes on the way and one
+// more pass that of the others; otherwise the sweeps, then the defect kernel.
+// The same d and norm either way.  A tiled level leaves the smoothed iterate in d
+// instead, and its coarse level ready.
 int presmooth_norm(rs_grid *G, int nu1, double *out)
 {
     LevelData &f = G->lev[0];
@@ -656,9 +657,8 @@ double wg_updates(const rs_grid *G, int l, int nu1, int nu2);
 // the tiles' arithmetic the longer way (a V(2,2) cycle of 513^2 209 plain, 225
 // in tiles).  There are few sizes between: 257x513 and its like (131 841 to
 // 135 201 nodes) take 4 to 12 % less in tiles, which this line leaves out.
-// RS_SWEEP (any sweep kernel picked by
-// hand) and profiling of the finest level's colour passes keep the plain
-// launches.
+// RS_SWEEP (any sweep kernel picked by hand) and profiling of the finest level's
+// colour passes keep the plain launches.
 constexpr long long kTileMaxNodes = 1ll << 17;
 
 // Which levels do is decided once, at the entry of a call that sweeps: the parts
